@@ -253,14 +253,18 @@ aqd_status_t qconv_run_proj(qconv_t conv, qconv_t proj, int level, int n, int h,
 
 void qconv_destroy(qconv_t conv);
 
-/* The arithmetic a handle's launches run on, fixed at create: "fp4-mfma"
+/* The arithmetic of a handle's own kernel, fixed at create: "fp4-mfma"
  * (2-bit codes and 2-bit weights with cin and cout multiples of 256, exact
- * while K * 3 * max|w| < 2^24: the scaled FP4 MFMA with e2m1 operands and
- * fp32 sums of integers), "i8-mfma" (codes widened to int8 on the int8
- * MFMA), "direct" (every other shape: one thread per output). A static
+ * while K * 3 * max|w| < 2^24: the FP4 MFMA with e2m1 operands and fp32 sums
+ * of integers), "i8-mfma" (codes widened to int8 on the int8 MFMA), "direct"
+ * (every other shape: one thread per output). Small launches, and launches
+ * that would run on the direct kernel, take a kernel that reads its operands
+ * straight from global memory where the shape allows (cin a multiple of 32,
+ * or of 16 for 8-bit codes): e2m3 or e2m1 operands with fp32 sums of integers
+ * below 2^24, int8 ones for 8-bit codes; the same results bit for bit. A static
  * string; "invalid" for a null handle. With the environment variable
- * AQD_NO_FP4=1 at create, 2-bit layers take the int8 MFMA path instead (the
- * same results; for comparing the two). */
+ * AQD_NO_FP4=1 at create, 2-bit layers' own kernel is the int8 MFMA's (the same
+ * results; for comparing the two). */
 const char *qconv_path(qconv_t conv);
 
 /* Standalone integer skip connection (Sec. 3.2.3, Eq. 7) with

@@ -236,7 +236,7 @@ def qconv_destroy(conv):
 
 
 def qconv_path(conv) -> str:
-    """'fp4-mfma', 'i8-mfma' or 'direct': the arithmetic of the handle's launches."""
+    """'fp4-mfma', 'i8-mfma' or 'direct': the arithmetic of the handle's own kernel (see aqd.h)."""
     return lib().qconv_path(conv).decode()
 
 

@@ -90,6 +90,65 @@ uint8_t e2m1_nibble(int v)
     return (uint8_t)((v < 0 ? 0x8 : 0x0) | mag[v < 0 ? -v : v]);
 }
 
+// F6 weights: position p of a 32-channel chunk holds channel e2m3_channel(p),
+// the order spread6 (mfma_common.h) leaves the codes in
+int e2m3_channel(int p)
+{
+    static const int order[16] = {0, 1, 3, 4, 6, 7, 9, 10, 12, 13, 15, 8, 2, 11, 5, 14};
+    return 16 * (p / 16) + order[p % 16];
+}
+
+// Weights of the global-fed kernel (internal.h): row r of row tile i of
+// 64-channel group ct is channel 64 ct + 16 (r / 4) + 4 i + r % 4 (a lane then
+// holds consecutive channels of its pixel); chunk g of K step ks is chunk
+// 4 ks + g of the window, taps in order; chunks past the window are zeros.
+// wv: decoded values [cout][taps][cin].
+std::vector<uint8_t> gf_weights(int kind, int cout, int taps, int cin, int groups, int steps, const int16_t *wv)
+{
+    const int ch = kind == GF_I8 ? 16 : 32, chunks = taps * (cin / ch);
+    const size_t tile = kind == GF_F6 ? GF_F6_TILE : 1024;
+    std::vector<uint8_t> out((size_t)groups * steps * 4 * tile, 0);
+    int order[32];
+    for (int p = 0; p < ch; ++p)
+        order[p] = kind == GF_F6 ? e2m3_channel(p) : kind == GF_F4 ? fp4_channel(p) : p;
+    for (int co = 0; co < cout; ++co) {
+        const int ct = co / 64, i = co % 16 / 4, r = 4 * (co % 64 / 16) + co % 4;
+        // (the chunks of a channel's taps are consecutive: cin is a multiple of ch)
+        for (int kc = 0; kc < chunks; ++kc) {
+            const int16_t *src = wv + (size_t)co * taps * cin + (size_t)kc * ch;
+            uint8_t *t = out.data() + (((size_t)ct * steps + kc / 4) * 4 + i) * tile;
+            const int lane = 16 * (kc % 4) + r;
+            if (kind == GF_F6) {
+                // e2m3 of w / 8: sign and magnitude, |w| <= 15; 16 fields of 6 bits
+                // per three words
+                uint32_t w[6];
+                for (int h = 0; h < 2; ++h) {
+                    uint64_t f[16];
+                    for (int p = 0; p < 16; ++p) {
+                        const int v = src[order[16 * h + p]];
+                        f[p] = v < 0 ? 32u - v : v;
+                    }
+                    const uint64_t lo = f[0] | f[1] << 6 | f[2] << 12 | f[3] << 18 | f[4] << 24 | f[5] << 30 |
+                                        f[6] << 36 | f[7] << 42 | f[8] << 48 | f[9] << 54 | f[10] << 60;
+                    w[3 * h] = (uint32_t)lo;
+                    w[3 * h + 1] = (uint32_t)(lo >> 32);
+                    w[3 * h + 2] = (uint32_t)(f[10] >> 4 | f[11] << 2 | f[12] << 8 | f[13] << 14 | f[14] << 20 |
+                                              f[15] << 26);
+                }
+                std::memcpy(t + 16 * lane, w, 16);
+                std::memcpy(t + 1024 + 8 * lane, w + 4, 8);
+            } else if (kind == GF_F4) {
+                for (int p = 0; p < 32; ++p)
+                    t[16 * lane + p / 2] |= (uint8_t)(e2m1_nibble(src[order[p]]) << (4 * (p % 2)));
+            } else {
+                for (int p = 0; p < 16; ++p)
+                    t[16 * lane + p] = (uint8_t)(int8_t)src[p];
+            }
+        }
+    }
+    return out;
+}
+
 int pick_tile(int cout, bool codes, int bits_in)
 {
     if (bits_in == 4 && cout >= 256 && (!codes || cout % 32 == 0))
@@ -136,12 +195,17 @@ struct qconv_s {
     bool mfma;
     int tile_cfg, blk_co, blk_px;
     int co_tiles, ksteps, cout_pad;
-    void *w_dev;
+    void *w_dev;       // the one allocation: weights, then the parts below
     int32_t *epi_dev;  // [num_levels][EPI_FIELDS][cout_pad]
     int32_t *lut_dev;  // code skips: [num_levels][cout_pad][2^skip_bits] RSM(k, c, d), else null
     std::vector<int> fast;  // per level: every shift >= 2
     std::vector<int> side0; // per level: every skip side is 0
     const uint8_t *zero;    // the device's zero page
+    // global-fed kernel: operand kind (GF_NONE: not available), 64-channel
+    // groups, K steps, weights and epilogue tables [num_levels][EPI_FIELDS][64 * gf_groups]
+    int gf_kind, gf_groups, gf_steps;
+    void *gf_w;
+    int32_t *gf_epi;
 };
 
 extern "C" {
@@ -219,17 +283,20 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
         return fail(AQD_ERR_UNSUPPORTED, "accumulator could exceed int32 for this K and bitwidths");
 
     // decode weight fields
+    int16_t value[256];
+    for (int f = 0; f < (1 << dc.bits_w); ++f)
+        value[f] = (int16_t)weight_value(f, dc.bits_w, d.wenc);
+    const int per = 8 / d.bits_w;
     const int wrow = d.cin * d.bits_w / 8;
     const int taps = d.kh * d.kw;
     std::vector<int16_t> wv((size_t)d.cout * taps * d.cin);
     for (int co = 0; co < d.cout; ++co)
         for (int t = 0; t < taps; ++t) {
             const uint8_t *row = w_packed + ((size_t)co * taps + t) * wrow;
-            for (int ci = 0; ci < d.cin; ++ci) {
-                int bit = ci * d.bits_w;
-                int f = (row[bit >> 3] >> (bit & 7)) & ((1 << dc.bits_w) - 1);
-                wv[((size_t)co * taps + t) * d.cin + ci] = (int16_t)weight_value(f, dc.bits_w, d.wenc);
-            }
+            int16_t *dst = wv.data() + ((size_t)co * taps + t) * d.cin;
+            for (int b = 0; b < wrow; ++b)
+                for (int e = 0; e < per; ++e)
+                    dst[b * per + e] = value[(row[b] >> (e * d.bits_w)) & ((1 << dc.bits_w) - 1)];
         }
 
     // MFMA kernel: 2/4-bit activations, weights that fit int8, 64-channel K
@@ -309,6 +376,9 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
         // nibble first) = e2m1 of the weight of input channel
         // fp4_channel(128 q + kappa) of the stage, q = K step % 2
         const int k4pt = d.cin / 128, ks4 = taps * k4pt;
+        int order[256];
+        for (int kap = 0; kap < 256; ++kap)
+            order[kap] = fp4_channel(kap);
         wbuf.assign((size_t)h.co_tiles * ks4 * 256 * 64, 0);
         for (int ct = 0; ct < h.co_tiles; ++ct)
             for (int ks = 0; ks < ks4; ++ks) {
@@ -319,13 +389,16 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
                     uint8_t *dst = wbuf.data() + (((size_t)ct * ks4 + ks) * 256 + rho) * 64;
                     const int16_t *src = wv.data() + ((size_t)co * taps + tap) * d.cin + stage0;
                     for (int kap = 0; kap < 128; ++kap)
-                        dst[kap / 2] |= (uint8_t)(e2m1_nibble(src[fp4_channel(128 * q + kap)]) << (4 * (kap % 2)));
+                        dst[kap / 2] |= (uint8_t)(e2m1_nibble(src[order[128 * q + kap]]) << (4 * (kap % 2)));
                 }
             }
     } else if (mfma) {
         // tiles [co_tile][k step][row rho][byte p]: channel tile_row_channel(rho) of the tile,
         // input channel widened_channel(p) of the K step's 64-channel chunk
         const int kpt = d.cin / KC;
+        int order[KC];
+        for (int p = 0; p < KC; ++p)
+            order[p] = widened_channel(d.bits_in, p);
         wbuf.assign((size_t)h.co_tiles * h.ksteps * BLK_CO * KC, 0);
         for (int ct = 0; ct < h.co_tiles; ++ct)
             for (int ks = 0; ks < h.ksteps; ++ks) {
@@ -337,7 +410,7 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
                     int8_t *dst = (int8_t *)wbuf.data() + (((size_t)ct * h.ksteps + ks) * BLK_CO + rho) * KC;
                     const int16_t *src = wv.data() + ((size_t)co * taps + tap) * d.cin + cc * KC;
                     for (int p = 0; p < KC; ++p)
-                        dst[p] = (int8_t)src[widened_channel(d.bits_in, p)];
+                        dst[p] = (int8_t)src[order[p]];
                 }
             }
     } else {
@@ -397,6 +470,44 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
             }
     }
 
+    // the global-fed kernel: 4-bit containers with weights of at most 4 bits and
+    // 2-bit codes with 2-bit weights while every sum stays exact in fp32, 8-bit
+    // codes with int8 weights while the re-centred bias fits int32
+    std::vector<uint8_t> gfw;
+    std::vector<int32_t> gfe;
+    if (!codes || d.cout % 4 == 0) {
+        const long long kmax = K * ((1 << dc.bits_in) - 1) * wmax;
+        if (dc.bits_in >= 3 && dc.bits_in <= 4 && dc.bits_w <= 4 && d.cin % 32 == 0 && kmax < (1LL << 24))
+            h.gf_kind = GF_F6;
+        else if (dc.bits_in == 2 && dc.bits_w == 2 && d.cin % 32 == 0 && kmax < (1LL << 24))
+            h.gf_kind = GF_F4;
+        else if (dc.bits_in == 8 && d.cin % 16 == 0 && w_fits_i8)
+            h.gf_kind = GF_I8;
+    }
+    if (h.gf_kind != GF_NONE) {
+        const int chunk = h.gf_kind == GF_I8 ? 16 : 32;
+        h.gf_groups = (d.cout + 63) / 64;
+        h.gf_steps = (taps * (d.cin / chunk) + 3) / 4;
+        gfw = gf_weights(h.gf_kind, d.cout, taps, d.cin, h.gf_groups, h.gf_steps, wv.data());
+        const int pad = 64 * h.gf_groups;
+        gfe.assign((size_t)d.num_levels * EPI_FIELDS * pad, 0);
+        for (int l = 0; l < d.num_levels && h.gf_kind != GF_NONE; ++l)
+            for (int f = 0; f < EPI_FIELDS; ++f)
+                std::memcpy(gfe.data() + ((size_t)l * EPI_FIELDS + f) * pad,
+                            epi.data() + ((size_t)l * EPI_FIELDS + f) * h.cout_pad, d.cout * sizeof(int32_t));
+        if (h.gf_kind == GF_I8 && !b8)   // (b8 tables are re-centred already)
+            for (int l = 0; l < d.num_levels; ++l)
+                for (int co = 0; co < d.cout; ++co) {
+                    long long sw = 0;
+                    for (size_t k = 0; k < (size_t)taps * d.cin; ++k)
+                        sw += wv[(size_t)co * taps * d.cin + k];
+                    const long long b = (long long)levels[l].bias[co] + 128 * sw;
+                    if (b < INT32_MIN || b > INT32_MAX)
+                        h.gf_kind = GF_NONE;   // runs on the direct kernel
+                    gfe[((size_t)l * EPI_FIELDS + EPI_BIAS) * pad + co] = (int32_t)b;
+                }
+    }
+
     const char *inject = std::getenv("AQD_FAULT_INJECT");
     if (inject && std::strcmp(inject, "alloc") == 0)
         return fail(AQD_ERR_NOMEM, "device allocation failed (injected)");
@@ -407,37 +518,38 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     qconv_s *hp = new (std::nothrow) qconv_s(h);
     if (!hp)
         return fail(AQD_ERR_NOMEM, "host allocation failed");
-    // MFMA weights: four K steps of 256-row tiles (64 KiB) of padding past the
-    // end, which the register-fed kernel's look-ahead may read (never use)
-    const size_t w_pad = mfma ? 4 * 256 * KC : 0;
-    if (hipMalloc(&hp->w_dev, wbuf.size() + w_pad) != hipSuccess) {
+    // one device allocation and copy for the weights, the tables and the skip
+    // tables (256-byte aligned parts). MFMA weights: four K steps of 256-row tiles
+    // (64 KiB) of padding past the end, which the register-fed kernel's
+    // look-ahead may read (never use)
+    auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
+    const size_t o_epi = up(wbuf.size() + (mfma ? 4 * 256 * KC : 0)), o_lut = o_epi + up(epi.size() * sizeof(int32_t)),
+                 o_gfw = o_lut + up(lut.size() * sizeof(int32_t)), o_gfe = o_gfw + up(gfw.size()),
+                 total = o_gfe + gfe.size() * sizeof(int32_t);
+    std::vector<uint8_t> blob(total, 0);
+    auto put = [&](size_t at, const void *src, size_t n) {
+        if (n)
+            std::memcpy(blob.data() + at, src, n);
+    };
+    put(0, wbuf.data(), wbuf.size());
+    put(o_epi, epi.data(), epi.size() * sizeof(int32_t));
+    put(o_lut, lut.data(), lut.size() * sizeof(int32_t));
+    put(o_gfw, gfw.data(), gfw.size());
+    put(o_gfe, gfe.data(), gfe.size() * sizeof(int32_t));
+    if (hipMalloc(&hp->w_dev, total) != hipSuccess) {
         delete hp;
-        return fail(AQD_ERR_NOMEM, "hipMalloc of the weights failed");
+        return fail(AQD_ERR_NOMEM, "hipMalloc of the weights and tables failed");
     }
-    if (hipMalloc((void **)&hp->epi_dev, epi.size() * sizeof(int32_t)) != hipSuccess) {
+    if (hipMemcpy(hp->w_dev, blob.data(), total, hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(hp->w_dev);
-        delete hp;
-        return fail(AQD_ERR_NOMEM, "hipMalloc of the epilogue tables failed");
-    }
-    hp->lut_dev = nullptr;
-    if (nk && hipMalloc((void **)&hp->lut_dev, lut.size() * sizeof(int32_t)) != hipSuccess) {
-        (void)hipFree(hp->w_dev);
-        (void)hipFree(hp->epi_dev);
-        delete hp;
-        return fail(AQD_ERR_NOMEM, "hipMalloc of the skip tables failed");
-    }
-    if (hipMemcpy(hp->w_dev, wbuf.data(), wbuf.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(hp->epi_dev, epi.data(), epi.size() * sizeof(int32_t), hipMemcpyHostToDevice) !=
-            hipSuccess ||
-        (nk && hipMemcpy(hp->lut_dev, lut.data(), lut.size() * sizeof(int32_t), hipMemcpyHostToDevice) !=
-                   hipSuccess)) {
-        (void)hipFree(hp->w_dev);
-        (void)hipFree(hp->epi_dev);
-        if (hp->lut_dev)
-            (void)hipFree(hp->lut_dev);
         delete hp;
         return fail(AQD_ERR_DEVICE, "copy of the weights to the device failed");
     }
+    uint8_t *base = (uint8_t *)hp->w_dev;
+    hp->epi_dev = (int32_t *)(base + o_epi);
+    hp->lut_dev = nk ? (int32_t *)(base + o_lut) : nullptr;
+    hp->gf_w = base + o_gfw;
+    hp->gf_epi = (int32_t *)(base + o_gfe);
     *out = hp;
     return AQD_OK;
 }
@@ -456,9 +568,6 @@ void qconv_destroy(qconv_t conv)
     if (!conv)
         return;
     (void)hipFree(conv->w_dev);
-    (void)hipFree(conv->epi_dev);
-    if (conv->lut_dev)
-        (void)hipFree(conv->lut_dev);
     delete conv;
 }
 
@@ -762,6 +871,99 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
     return AQD_OK;
 }
 
+// Whether a checked group runs on the global-fed kernel (mfma: its handles have
+// a tiled kernel), and its launch. t64 counts 64 x 64 tiles,
+// steps the K steps. Measured on MI355X, us per launch, own kernel -> global-fed:
+//  * at most 512 tiles (two per CU): 3x3 256 -> 256 on 4200 pixels 27.6 -> 11.3,
+//    1x1 2048 -> 512 on 1050 pixels 21 -> 7.4, 3x3 stride 2 2048 -> 256 on 273
+//    pixels 30 -> 21, on 2184 pixels 37 -> 29, 3x3 64 -> 64 on 1024 pixels 14.9 ->
+//    4.6. Above (528 tiles) the tiled kernels fill the GPU: 1x1 1024 -> 256 on
+//    8400 pixels 8.4 -> 9.9, 3x3 256 -> 256 13.7 -> 15.5;
+//  * up to 1100 tiles where the own tiles have 64 or 128 channels and K is more
+//    than the streaming kernels' (3x3 64 -> 64 on 66800 pixels 15.3 -> 10.0, 3x3
+//    128 -> 128 on 33400 pixels 18.3 -> 13.3, 3x3 256 -> 36 on 66800 pixels 35.7 ->
+//    22.9; at 2088 tiles 14.8 -> 15.7), or on the FP4 tiles (3x3 256 -> 256 on
+//    8400 pixels 15.2 -> 10.2; at 1056 tiles 15.5 -> 15.5);
+//  * any size for 2-bit layers with code outputs off the FP4 tiles (3x3 64 -> 64 on 534400 pixels
+//    37.4 -> 32.3, 3x3 128 -> 128 on 133600 pixels 35.2 -> 24.4: the int8 kernel
+//    widens every fragment and runs at half the MFMA rate) and for what otherwise
+//    runs one thread per output (3x3 256 -> 1 on 44600 pixels: 1470 -> 8).
+bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, bool mfma, MfmaArgs *out, GfPlan *plan)
+{
+    const qconv_s &h0 = *segs[0].conv;
+    if (h0.gf_kind == GF_NONE)
+        return false;
+    const int steps = h0.gf_steps;
+    long long t64 = 0;
+    for (int i = 0; i < count; ++i) {
+        if (segs[i].conv->gf_kind != h0.gf_kind || chk[i].xbytes >= (1ull << 31))
+            return false;
+        t64 += ((long long)segs[i].n * chk[i].ho * chk[i].wo + 63) / 64 * h0.gf_groups;
+    }
+    const bool narrow = h0.tile_cfg == TILE_128x256 || h0.tile_cfg == TILE_64x512;
+    if (mfma && t64 > 512 && !(narrow && h0.gf_kind == GF_F4 && h0.d.out_mode == AQD_OUT_CODES) &&
+        !(t64 <= 1100 && ((narrow && steps > 2) || h0.tile_cfg == TILE_FP4)))
+        return false;
+    // the waves of a tile split its K range while there are too few tiles to
+    // give every SIMD two waves; very few tiles are halved as well. 3x3 128 -> 128
+    // on 16700 pixels (522 tiles), 1 / 2 / 4 waves: 9.9 / 9.1 / 11.1 us; 3x3 64 ->
+    // 64 on 66800 (1044): 10.0 / 12.3 / 13.1; 3x3 256 -> 256 on 4200 (264): 12.7 /
+    // 12.7 / 11.3; 3x3 stride 2 256 -> 256 on 77 (8): 11.9 / 8.1 / 7.2, halved 6.1
+    *plan = GfPlan{h0.gf_kind, 4, 4, t64 > 1000 ? 1 : t64 > 400 ? 2 : 4};
+    if (t64 <= 100)
+        plan->nj = 2;
+    if (h0.d.cout <= 4)   // one row tile holds every channel
+        *plan = GfPlan{h0.gf_kind, 1, 4, 4};
+    else if (steps < plan->kw)
+        plan->kw = steps < 2 ? 1 : 2;
+    const int groups = plan->mi == 1 ? 1 : h0.gf_groups;
+    const int px = 16 * plan->nj;
+    MfmaArgs &a = *out;
+    a = MfmaArgs{};
+    long long tiles = 0;
+    for (int i = 0; i < count; ++i) {
+        const qconv_seg_t &s = segs[i];
+        if (s.n == 0)
+            continue;
+        MfmaSeg &m = a.seg[a.nseg++];
+        m.x = (const uint8_t *)s.x;
+        m.skip = s.skip;
+        m.y = s.y;
+        m.wt = (const int8_t *)s.conv->gf_w;
+        m.epi = s.conv->gf_epi + (size_t)s.level * EPI_FIELDS * 64 * s.conv->gf_groups;
+        m.P = (long long)s.n * chk[i].ho * chk[i].wo;
+        m.n = s.n;
+        m.h = s.h;
+        m.w = s.w;
+        m.ho = chk[i].ho;
+        m.wo = chk[i].wo;
+        m.hs = s.hs;
+        m.ws = s.ws;
+        m.tile_begin = (int)tiles;
+        m.fast = s.conv->fast[s.level];
+        tiles += (m.P + px - 1) / px * groups;
+        if (tiles >= (1LL << 26))
+            return false;
+    }
+    a.total_tiles = (int)tiles;
+    a.tiles_per_xcd = (a.total_tiles + 7) / 8;
+    a.ksplit = 1;
+    a.cin = h0.d.cin;
+    a.cout = h0.d.cout;
+    a.cout_pad = 64 * h0.gf_groups;
+    a.kh = h0.d.kh;
+    a.kw = h0.d.kw;
+    a.stride = h0.d.stride;
+    a.pad = h0.d.pad;
+    a.co_tiles = groups;
+    a.ksteps = a.kchunk = h0.gf_steps;
+    a.up2 = h0.d.skip_up2;
+    a.bits_out = h0.d.out_mode == AQD_OUT_INT32 ? 32 : h0.d.bits_out;
+    a.qmax = h0.qmax;
+    a.skip_bits = h0.d.skip_bits;
+    return true;
+}
+
 // Split of the K range: the number of parts minimising a simple model of the
 // MI355X (256 CUs, two workgroups per CU), fitted to measured launches: a
 // workgroup alone on its CU takes ~0.65 us per K step, two sharing a CU
@@ -888,6 +1090,14 @@ aqd_status_t run_group(int count, const qconv_seg_t *segs, void *workspace, size
     aqd_status_t st = prepare_group(count, segs, chk, &a, &direct);
     if (st != AQD_OK)
         return st;
+    MfmaArgs ga;
+    GfPlan gp;
+    const bool gf = plan_gf(count, segs, chk, !direct, &ga, &gp);
+    if (direct && gf) {
+        if (ga.nseg && launch_qconv_gf(ga, gp, stream) != hipSuccess)
+            return fail(AQD_ERR_DEVICE, "global-fed conv launch failed");
+        return AQD_OK;
+    }
     if (direct) {
         for (int i = 0; i < count; ++i)
             if (segs[i].n > 0) {
@@ -920,6 +1130,11 @@ aqd_status_t run_group(int count, const qconv_seg_t *segs, void *workspace, size
         plan_split(a, &nparts, &kchunk);
         if (nparts > 1 && ws_bytes < split_bytes(a, nparts))
             nparts = 1;
+    }
+    if (gf) {
+        if (launch_qconv_gf(ga, gp, stream) != hipSuccess)
+            return fail(AQD_ERR_DEVICE, "global-fed conv launch failed");
+        return AQD_OK;
     }
     if (nparts == 1) {
         if (launch_qconv_mfma(h0.d.bits_in, a, stream) != hipSuccess)

@@ -117,6 +117,21 @@ hipError_t launch_qconv_wv_proj(const MfmaArgs &a, hipStream_t stream);
 // TILE_FP4 (code_bits 2) and TILE_B8 (code_bits 8) launches (qconv_b16.hip);
 // a.ksteps and a.kchunk in 64-channel steps, multiples of a stage (4 and 2)
 hipError_t launch_qconv_b16(int code_bits, const MfmaArgs &a, hipStream_t stream);
+// Global-fed launches (qconv_gf.hip): operand kinds of the weights stored for
+// them at create ([64-channel group][K step][4 row tiles][WB bytes], WB =
+// GF_F6_TILE for e2m3, else 1024; per row tile the 16 bytes of each lane, then
+// for e2m3 8 more; a lane: row lane % 16, chunk lane / 16 of the K step)
+enum { GF_NONE = 0, GF_F6 = 1, GF_F4 = 2, GF_I8 = 3 };
+constexpr int GF_F6_TILE = 1536;
+// mi 16-channel row tiles x nj 16-pixel column tiles per workgroup of kw
+// waves, which split the K range
+struct GfPlan {
+    int kind, mi, nj, kw;
+};
+// a.co_tiles counts workgroup tiles (4 / mi per 64-channel group), a.ksteps
+// steps of four chunks (32 channels, or 16 of 8-bit codes); the segments' wt and
+// epi are the stored gf weights and tables (cout_pad a multiple of 64)
+hipError_t launch_qconv_gf(const MfmaArgs &a, const GfPlan &p, hipStream_t stream);
 // TILE_STEM launches (qconv_stem.hip); weights [co_tile][3][64 rows][64 B]
 hipError_t launch_qconv_stem(const MfmaArgs &a, hipStream_t stream);
 

@@ -51,6 +51,37 @@ __device__ __forceinline__ uint2 load_b64(buf_rsrc r, int voff, int soff)
 }
 
 
+// 16 codes of 4 bits (words a, b) -> 16 e2m3 values in 6-bit fields (three
+// words): the field of a code is the code itself, zero extended (code / 8 in
+// e2m3), so each code moves to a field at a multiple of 6 bits. The codes keep
+// the offset they have modulo 4 or move up by 2, which takes them in the order
+// e2m3_channel (aqd_api.hip; the weights were stored in that order): 8
+// instructions for 16 codes.
+__device__ __forceinline__ void spread6(uint32_t a, uint32_t b, int &d0, int &d1, int &d2)
+{
+    const uint32_t t = a << 2, w = __builtin_amdgcn_alignbit(b, a, 30);  // w = b << 2 | a >> 30
+    d0 = (int)((a & 0x0F00F00Fu) | (t & 0xC03C03C0u));
+    d1 = (int)((b & 0xF00F00F0u) | (w & 0x03C03C03u));
+    d2 = (int)((a & 0x00F00F00u) | (w & 0x3C03C03Cu));
+}
+typedef int v8i __attribute__((ext_vector_type(8)));
+// an MFMA operand (32 channels of a lane) from its packed 4-bit or 2-bit codes;
+// the instruction reads 6 (e2m3) or 4 (e2m1) of the 8 registers
+__device__ __forceinline__ v8i spread_e2m3(const v4i x)
+{
+    v8i o = {0, 0, 0, 0, 0, 0, 0, 0};
+    int d0, d1, d2, d3, d4, d5;
+    spread6((uint32_t)x.x, (uint32_t)x.y, d0, d1, d2);
+    spread6((uint32_t)x.z, (uint32_t)x.w, d3, d4, d5);
+    o[0] = d0; o[1] = d1; o[2] = d2; o[3] = d3; o[4] = d4; o[5] = d5;
+    return o;
+}
+__device__ __forceinline__ v8i spread_e2m1(const uint2 x)
+{
+    return v8i{(int)(x.x & 0x33333333u), (int)((x.x >> 2) & 0x33333333u),
+               (int)(x.y & 0x33333333u), (int)((x.y >> 2) & 0x33333333u), 0, 0, 0, 0};
+}
+
 // round(a * c / 2^d), ties up, d in [0, 31], result modulo 2^32: one 64-bit
 // multiply-add (exact: |a*c| < 2^62) and a funnel shift. The rounding term
 // 2^(d-1) (0 for d = 0) is (2^d) / 2 in 32 bits (below 2^31: a zero high

@@ -53,7 +53,6 @@ namespace aqd {
 namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
-typedef int v8i __attribute__((ext_vector_type(8)));
 
 constexpr int F4_BCO = 256;                   // channels per workgroup tile
 constexpr int F4_BPX = 128;                   // pixels per workgroup tile

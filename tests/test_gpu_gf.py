@@ -1,0 +1,72 @@
+"""Parity of the global-fed kernel (operands straight from global memory, the
+waves of a tile splitting its K range) against the oracle, bit for bit: every
+tile and split its rule picks (64 x 64 tiles on 1, 2 and 4 waves, 64 x 32 on
+4, 16 channels x 64 pixels for at most 4 channels), the three operand formats,
+every output and skip width, steps that span taps, partial channel groups and
+pixel tiles, and sums at the bound where fp32 stops being exact."""
+import numpy as np
+import pytest
+
+from gpu_helpers import assert_same, check_case, gpu_conv, oracle_conv
+from paper_2007_06919_amd import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available()
+    return t
+
+
+CASES = {
+    # <= 100 tiles: 64 x 32, 4 waves
+    "f6_k5_two_taps_a_step": dict(n=1, h=32, w=32, cin=64, cout=64, k=3),
+    "f6_up2_skip": dict(n=2, h=13, w=21, cin=256, cout=256, k=3, skip_bits=4, skip_up2=True, wenc=1),
+    "f6_cin96_partial_group_int32": dict(n=1, h=9, w=11, cin=96, cout=80, k=3, stride=2, bits_out=32, wenc=1),
+    "f6_cin32_one_step": dict(n=1, h=9, w=11, cin=32, cout=36, k=1, bits_out=32),
+    "f6_cout20_kernel5": dict(n=1, h=17, w=5, cin=64, cout=20, k=5),
+    "f6_int32_skip": dict(n=1, h=17, w=5, cin=128, cout=256, k=1, skip_bits=32, wenc=1),
+    "f6_8bit_out": dict(n=2, h=7, w=11, cin=256, cout=256, k=3, bits_out=8, wenc=1),
+    "f6_3bit_levels": dict(n=2, h=7, w=11, cin=64, cout=64, k=3, bits_in=3, bits_w=3, bits_out=3, skip_bits=3,
+                           wenc=1, num_levels=2),
+    "f4_skip": dict(n=1, h=9, w=11, cin=128, cout=128, k=3, bits_in=2, bits_w=2, bits_out=2, skip_bits=2, wenc=1),
+    "i8_int32": dict(n=2, h=7, w=11, cin=128, cout=36, k=3, bits_in=8, bits_w=8, bits_out=32),
+    "i8_8bit_out_skip": dict(n=2, h=7, w=11, cin=48, cout=40, k=3, bits_in=8, bits_w=4, bits_out=8, skip_bits=8),
+    "i8_int32_skip_cin16": dict(n=1, h=7, w=11, cin=16, cout=12, k=3, bits_in=8, bits_w=8, bits_out=4, skip_bits=32),
+    # 1 to 4 channels
+    "f6_cout1": dict(n=2, h=13, w=21, cin=256, cout=1, k=3, bits_out=32, wenc=1),
+    "f6_cout3": dict(n=2, h=7, w=9, cin=64, cout=3, k=1, bits_out=32, wenc=1),
+    "f6_cout4_codes": dict(n=2, h=13, w=21, cin=64, cout=4, k=3),
+    "f4_cout2_long_k": dict(n=2, h=13, w=21, cin=2048, cout=2, k=3, bits_in=2, bits_w=2, bits_out=32),
+    # 101 - 400 tiles: 64 x 64, 4 waves (2 steps: 2 waves)
+    "f6_4waves": dict(n=1, h=50, w=45, cin=256, cout=256, k=3, wenc=1),
+    "f6_1x1_two_steps": dict(n=1, h=50, w=45, cin=256, cout=128, k=1, skip_bits=4),
+    # 401 - 1000 tiles: 2 waves; more: 1 wave
+    "f6_2waves_int32": dict(n=1, h=89, w=133, cin=128, cout=132, k=3, bits_out=32, wenc=1),
+    "f6_1wave": dict(n=1, h=179, w=361, cin=64, cout=64, k=3, wenc=1),
+    "f4_1wave_stride2": dict(n=2, h=181, w=339, cin=64, cout=192, k=3, stride=2, bits_in=2, bits_w=2, bits_out=2),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_global_fed_parity(torch, name):
+    check_case(torch, seed=700 + len(name), **CASES[name])
+
+
+@pytest.mark.parametrize("bits, cin, k", [(4, 8192, 3), (3, 16384, 3), (2, 16384, 5)])
+def test_sums_at_the_exact_bound(torch, bits, cin, k):
+    """All weights at the largest odd-grid value, all codes at the largest
+    but a few 1s (and some negative weights in the second channel half): sums up
+    to K * (2^b - 1)^2, just below 2^24 at 4 bits, exact in every term order."""
+    q = (1 << bits) - 1
+    assert cin * k * k * q * q < 1 << 24
+    case = workloads.random_conv_case(seed=31 + bits, n=1, h=5, w=6, cin=cin, cout=64, k=k, bits_in=bits,
+                                      bits_w=bits, wenc=1, bits_out=32)
+    rng = np.random.Generator(np.random.PCG64(bits))
+    case.x[:] = q
+    case.x[rng.random(case.x.shape) < 0.01] = 1
+    case.w_fields[:] = q
+    case.w_fields[32:][rng.random(case.w_fields[32:].shape) < 0.05] = 0
+    assert_same(gpu_conv(case, torch)[0], oracle_conv(case), f"{bits}-bit sums near 2^24")
