@@ -477,9 +477,10 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     std::vector<int32_t> gfe;
     if (!codes || d.cout % 4 == 0) {
         const long long kmax = K * ((1 << dc.bits_in) - 1) * wmax;
+        const bool off2 = no_fp4 && std::strcmp(no_fp4, "1") == 0;   // 2-bit layers on int8
         if (dc.bits_in >= 3 && dc.bits_in <= 4 && dc.bits_w <= 4 && d.cin % 32 == 0 && kmax < (1LL << 24))
             h.gf_kind = GF_F6;
-        else if (dc.bits_in == 2 && dc.bits_w == 2 && d.cin % 32 == 0 && kmax < (1LL << 24))
+        else if (!off2 && dc.bits_in == 2 && dc.bits_w == 2 && d.cin % 32 == 0 && kmax < (1LL << 24))
             h.gf_kind = GF_F4;
         else if (dc.bits_in == 8 && d.cin % 16 == 0 && w_fits_i8)
             h.gf_kind = GF_I8;
@@ -871,29 +872,40 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
     return AQD_OK;
 }
 
-// Whether a checked group runs on the global-fed kernel (mfma: its handles have
-// a tiled kernel), and its launch. t64 counts 64 x 64 tiles,
-// steps the K steps. Measured on MI355X, us per launch, own kernel -> global-fed:
-//  * at most 512 tiles (two per CU): 3x3 256 -> 256 on 4200 pixels 27.6 -> 11.3,
-//    1x1 2048 -> 512 on 1050 pixels 21 -> 7.4, 3x3 stride 2 2048 -> 256 on 273
-//    pixels 30 -> 21, on 2184 pixels 37 -> 29, 3x3 64 -> 64 on 1024 pixels 14.9 ->
-//    4.6. Above (528 tiles) the tiled kernels fill the GPU: 1x1 1024 -> 256 on
-//    8400 pixels 8.4 -> 9.9, 3x3 256 -> 256 13.7 -> 15.5;
-//  * up to 1100 tiles where the own tiles have 64 or 128 channels and K is more
-//    than the streaming kernels' (3x3 64 -> 64 on 66800 pixels 15.3 -> 10.0, 3x3
-//    128 -> 128 on 33400 pixels 18.3 -> 13.3, 3x3 256 -> 36 on 66800 pixels 35.7 ->
-//    22.9; at 2088 tiles 14.8 -> 15.7), or on the FP4 tiles (3x3 256 -> 256 on
-//    8400 pixels 15.2 -> 10.2; at 1056 tiles 15.5 -> 15.5);
-//  * any size for 2-bit layers with code outputs off the FP4 tiles (3x3 64 -> 64 on 534400 pixels
-//    37.4 -> 32.3, 3x3 128 -> 128 on 133600 pixels 35.2 -> 24.4: the int8 kernel
-//    widens every fragment and runs at half the MFMA rate) and for what otherwise
-//    runs one thread per output (3x3 256 -> 1 on 44600 pixels: 1470 -> 8).
-bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, bool mfma, MfmaArgs *out, GfPlan *plan)
+// The launch of a checked group on the block-float kernels (global-fed: qconv_gf,
+// tiled: qconv_fx), if they are the better choice over the handles' own kernel
+// (own: its tile, -1: the direct kernel). t64 counts tiles of 64 x 64 outputs,
+// steps K steps of 128 channels (64 of 8-bit codes). Measured on MI355X, us per
+// launch in a graph of 20, own -> new (P pixels; "gf n" n waves, "fx a x b" tiles):
+//  * t64 <= 512 (two tiles per CU): gf. 3x3 256 -> 256 P 4200 27.6 -> 11.3; 1x1 2048
+//    -> 512 P 1050 21 -> 7.4; 3x3 stride 2 2048 -> 256 P 273 30 -> 21, P 2184 37 -> 29;
+//    3x3 64 -> 64 P 1024 14.9 -> 4.6. So do the shapes of the direct kernel, at any
+//    size (3x3 256 -> 1 P 44600 1470 -> 8);
+//  * 64- and 128-channel layers of 4 bits up to t64 1100, K beyond the streaming
+//    kernels' two steps: gf. 3x3 64 -> 64 P 66800 15.3 -> 10.0 (t64 2088: 14.8 ->
+//    15.7), 3x3 128 -> 128 P 33400 18.3 -> 13.3, 3x3 256 -> 36 P 66800 35.7 -> 22.9;
+//    above, fx 128 x 128 for 65 to 128 channels and 9 steps or more, int32 at any
+//    size (3x3 256 -> 80 P 133600 54.9 -> 47.4), codes up to t64 1500 (3x3 128 -> 128
+//    stride 2 P 33400 18.9 -> 13.4, P 66800 19.6 -> 21.1);
+//  * 256-channel tiles of 4 bits, 9 steps or more: fx 256 x 128, 256 x 64 while that
+//    leaves the chip short of tiles. 3x3 256 -> 256 P 133600 73.9 -> 57.9, P 16700
+//    23.9 -> 16.5; 3x3 512 -> 512 P 8400 39.9 -> 25.0, P 4200 22.6 -> 17.4; 3x3 256 ->
+//    720 int32 P 133600 225 -> 175; 1x1 2048 -> 512 P 8400 20.8 -> 15.2. 8 steps: fx
+//    up to t64 1100 (1x1 1024 -> 256 P 16800 12.6 -> 10.4, P 33600 13.9 -> 15.1).
+//    One-round launches of the 256 x 144 tiles stay (P 33600 22.5 -> 23.6);
+//  * 2 bits (half the int8 kernels' time or less everywhere but in 1x1 layers of 64
+//    channels on many pixels, 81 -> 91, and 64-channel int32 layers): gf up to 64
+//    channels (3x3 64 -> 64 P 534400 37.4 -> 32.3), up to t64 1100 for 65 to 128, and
+//    for int32 skips (1x1 256 -> 1024 P 33600 75.9 -> 56.3); else fx: 3x3 128 -> 128 P
+//    133600 35.2 -> 20.7 (128 x 128), 3x3 256 -> 256 P 267200 96 -> 79.5 (256 x 128),
+//    P 33600 21.8 -> 16.2 (256 x 64), 1x1 512 -> 128 P 133600 24.2 -> 14.9.
+bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, MfmaArgs *out, GfPlan *plan)
 {
     const qconv_s &h0 = *segs[0].conv;
     if (h0.gf_kind == GF_NONE)
         return false;
-    const int steps = h0.gf_steps;
+    const int steps = h0.gf_steps, cout = h0.d.cout;
+    const bool f4 = h0.gf_kind == GF_F4, codes = h0.d.out_mode == AQD_OUT_CODES, mfma = own >= 0;
     long long t64 = 0;
     for (int i = 0; i < count; ++i) {
         if (segs[i].conv->gf_kind != h0.gf_kind || chk[i].xbytes >= (1ull << 31))
@@ -901,23 +913,46 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, bool mfma,
         t64 += ((long long)segs[i].n * chk[i].ho * chk[i].wo + 63) / 64 * h0.gf_groups;
     }
     const bool narrow = h0.tile_cfg == TILE_128x256 || h0.tile_cfg == TILE_64x512;
-    if (mfma && t64 > 512 && !(narrow && h0.gf_kind == GF_F4 && h0.d.out_mode == AQD_OUT_CODES) &&
-        !(t64 <= 1100 && ((narrow && steps > 2) || h0.tile_cfg == TILE_FP4)))
+    bool gf = !mfma || t64 <= 512;
+    if (!gf && f4)
+        gf = h0.d.skip_bits == 32 || (cout <= 64 && (codes || t64 <= 1100)) || (cout <= 128 && t64 <= 1100);
+    else if (!gf && h0.gf_kind == GF_F6)
+        gf = narrow && steps > 2 && t64 <= 1100;
+    // waves along channels and column tiles of the tiled kernel
+    int wc = 0, nj = 4;
+    if (!gf && h0.gf_kind != GF_I8 &&
+        (codes ? cout % 16 == 0 && h0.d.bits_out == h0.d.bits_in && h0.d.skip_bits != 32 &&
+                     (h0.d.skip_bits == 0 || h0.d.skip_bits == h0.d.bits_in)
+               : cout % 4 == 0)) {
+        if (f4 && cout > 64 && !(h0.d.cin == 64 && h0.d.kh == 1 && t64 > 8000)) {
+            wc = cout <= 128 ? 2 : 4;
+            nj = wc == 4 && t64 > (codes ? 12000 : 4000) ? 8 : 4;
+        } else if (!f4 && narrow && cout > 64 && steps >= 9 && (!codes || t64 <= 1500)) {
+            wc = 2;
+        } else if (!f4 && !narrow && own != TILE_WV144 &&
+                   (steps >= 9 || (steps == 8 && t64 <= 1100 && h0.d.skip_bits == 0))) {
+            wc = 4;
+            nj = t64 > 1024 && h0.d.skip_bits == 0 ? 8 : 4;
+        }
+    }
+    if (!gf && !wc)
         return false;
-    // the waves of a tile split its K range while there are too few tiles to
-    // give every SIMD two waves; very few tiles are halved as well. 3x3 128 -> 128
-    // on 16700 pixels (522 tiles), 1 / 2 / 4 waves: 9.9 / 9.1 / 11.1 us; 3x3 64 ->
-    // 64 on 66800 (1044): 10.0 / 12.3 / 13.1; 3x3 256 -> 256 on 4200 (264): 12.7 /
-    // 12.7 / 11.3; 3x3 stride 2 256 -> 256 on 77 (8): 11.9 / 8.1 / 7.2, halved 6.1
-    *plan = GfPlan{h0.gf_kind, 4, 4, t64 > 1000 ? 1 : t64 > 400 ? 2 : 4};
-    if (t64 <= 100)
-        plan->nj = 2;
-    if (h0.d.cout <= 4)   // one row tile holds every channel
-        *plan = GfPlan{h0.gf_kind, 1, 4, 4};
-    else if (steps < plan->kw)
-        plan->kw = steps < 2 ? 1 : 2;
-    const int groups = plan->mi == 1 ? 1 : h0.gf_groups;
-    const int px = 16 * plan->nj;
+    if (wc)
+        *plan = GfPlan{h0.gf_kind, wc, nj, 0};
+    else {
+        // the waves of a tile split its K range while there are too few tiles to
+        // give every SIMD two waves; very few tiles are halved as well. 3x3 128 ->
+        // 128 P 16700 (522 tiles), 1 / 2 / 4 waves: 9.9 / 9.1 / 11.1 us; 3x3 64 -> 64
+        // P 66800 (1044): 10.0 / 12.3 / 13.1; 3x3 256 -> 256 P 4200 (264): 12.7 / 12.7 /
+        // 11.3; 3x3 stride 2 256 -> 256 P 77 (8): 11.9 / 8.1 / 7.2, halved 6.1
+        *plan = GfPlan{h0.gf_kind, 4, t64 <= 100 ? 2 : 4, t64 > 1000 ? 1 : t64 > 400 ? 2 : 4};
+        if (cout <= 4)   // one row tile holds every channel
+            *plan = GfPlan{h0.gf_kind, 1, 4, 4};
+        else if (steps < plan->kw)
+            plan->kw = steps < 2 ? 1 : 2;
+    }
+    const int groups = wc ? (h0.gf_groups + wc - 1) / wc : plan->mi == 1 ? 1 : h0.gf_groups;
+    const int px = wc ? 16 * nj * (4 / wc) : 16 * plan->nj;
     MfmaArgs &a = *out;
     a = MfmaArgs{};
     long long tiles = 0;
@@ -941,6 +976,9 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, bool mfma,
         m.ws = s.ws;
         m.tile_begin = (int)tiles;
         m.fast = s.conv->fast[s.level];
+        m.side0 = s.conv->side0[s.level];
+        m.lut = s.conv->lut_dev ? s.conv->lut_dev + (size_t)s.level * s.conv->cout_pad * (1 << h0.d.skip_bits)
+                                : nullptr;
         tiles += (m.P + px - 1) / px * groups;
         if (tiles >= (1LL << 26))
             return false;
@@ -962,6 +1000,11 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, bool mfma,
     a.qmax = h0.qmax;
     a.skip_bits = h0.d.skip_bits;
     return true;
+}
+
+hipError_t launch_gf(const MfmaArgs &a, const GfPlan &p, hipStream_t stream)
+{
+    return p.kw == 0 ? launch_qconv_fx(a, p, stream) : launch_qconv_gf(a, p, stream);
 }
 
 // Split of the K range: the number of parts minimising a simple model of the
@@ -1092,9 +1135,9 @@ aqd_status_t run_group(int count, const qconv_seg_t *segs, void *workspace, size
         return st;
     MfmaArgs ga;
     GfPlan gp;
-    const bool gf = plan_gf(count, segs, chk, !direct, &ga, &gp);
+    const bool gf = plan_gf(count, segs, chk, direct ? -1 : a.tile_cfg, &ga, &gp);
     if (direct && gf) {
-        if (ga.nseg && launch_qconv_gf(ga, gp, stream) != hipSuccess)
+        if (ga.nseg && launch_gf(ga, gp, stream) != hipSuccess)
             return fail(AQD_ERR_DEVICE, "global-fed conv launch failed");
         return AQD_OK;
     }
@@ -1132,7 +1175,7 @@ aqd_status_t run_group(int count, const qconv_seg_t *segs, void *workspace, size
             nparts = 1;
     }
     if (gf) {
-        if (launch_qconv_gf(ga, gp, stream) != hipSuccess)
+        if (launch_gf(ga, gp, stream) != hipSuccess)
             return fail(AQD_ERR_DEVICE, "global-fed conv launch failed");
         return AQD_OK;
     }

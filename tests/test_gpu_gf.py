@@ -50,6 +50,48 @@ CASES = {
 }
 
 
+# tiled kernel: 256 x 128, 256 x 64 and 128 x 128 tiles, stages that span taps
+# (cin 32 to 96) or end in the middle (odd step counts), partial channel tiles
+# (more than one group past the last), ragged pixel tiles, skips of mixed and
+# zero sides, the 64-bit requantisation (shifts below 2)
+TILED = {
+    "f6_256x128": dict(n=2, h=97, w=91, cin=256, cout=256, k=3, wenc=1),
+    "f6_256x128_partial_cout": dict(n=1, h=97, w=91, cin=128, cout=592, k=3, wenc=1),
+    "f6_256x128_int32": dict(n=1, h=75, w=91, cin=160, cout=720, k=3, bits_out=32, wenc=1),
+    "f6_256x64": dict(n=1, h=67, w=75, cin=1024, cout=512, k=1),
+    "f6_256x64_skip_cin96": dict(n=1, h=83, w=75, cin=160, cout=512, k=3, skip_bits=4),
+    "f6_256x64_3bit": dict(n=1, h=83, w=75, cin=192, cout=384, k=3, bits_in=3, bits_w=3, bits_out=3, wenc=1),
+    "f6_128x128_int32": dict(n=2, h=131, w=141, cin=160, cout=80, k=3, bits_out=32, wenc=1),
+    "f6_128x128_stride2": dict(n=2, h=261, w=251, cin=128, cout=128, k=3, stride=2, wenc=1),
+    "f4_256x128": dict(n=2, h=299, w=331, cin=32, cout=256, k=3, bits_in=2, bits_w=2, bits_out=2, wenc=1),
+    "f4_256x64_skip_up2": dict(n=1, h=83, w=75, cin=256, cout=512, k=1, bits_in=2, bits_w=2, bits_out=2, skip_bits=2,
+                               skip_up2=True),
+    "f4_256x128_int32": dict(n=1, h=201, w=203, cin=96, cout=516, k=3, bits_in=2, bits_w=2, bits_out=32, wenc=1),
+    "f4_128x128": dict(n=2, h=131, w=141, cin=96, cout=112, k=3, bits_in=2, bits_w=2, bits_out=2, skip_bits=2),
+}
+
+
+@pytest.mark.parametrize("name", TILED)
+def test_tiled_parity(torch, name):
+    check_case(torch, seed=800 + len(name), **TILED[name])
+
+
+@pytest.mark.parametrize("bits, skip", [(4, 0), (4, 4), (2, 0), (2, 2)])
+def test_tiled_epilogue_forms(torch, bits, skip):
+    """64-bit requantisation (a shift below 2), and skips whose sides are all 0
+    (the table of scaled codes)."""
+    for form in ("slow", "side0"):
+        case = workloads.random_conv_case(seed=61 + bits, n=1, h=83, w=75, cin=512, cout=512, k=3, bits_in=bits,
+                                          bits_w=bits, bits_out=bits, skip_bits=skip)
+        lv = case.levels[0]
+        if form == "slow":
+            lv["shift"][5] = 1
+            lv["mult"][5] = 1 << 30
+        elif skip:
+            lv["skip_side"][:] = 0
+        assert_same(gpu_conv(case, torch)[0], oracle_conv(case), f"{bits}-bit {form}")
+
+
 @pytest.mark.parametrize("name", CASES)
 def test_global_fed_parity(torch, name):
     check_case(torch, seed=700 + len(name), **CASES[name])
