@@ -90,12 +90,14 @@ uint8_t e2m1_nibble(int v)
     return (uint8_t)((v < 0 ? 0x8 : 0x0) | mag[v < 0 ? -v : v]);
 }
 
-// F6 weights: position p of a 32-channel chunk holds channel e2m3_channel(p),
-// the order spread6 (mfma_common.h) leaves the codes in
-int e2m3_channel(int p)
+// 16 nibbles of two words to 6-bit fields: the kernels' spread6 (mfma_common.h),
+// whose channel order the weights therefore share
+void host_spread6(uint32_t a, uint32_t b, uint32_t *d)
 {
-    static const int order[16] = {0, 1, 3, 4, 6, 7, 9, 10, 12, 13, 15, 8, 2, 11, 5, 14};
-    return 16 * (p / 16) + order[p % 16];
+    const uint32_t t = a << 2, w = b << 2 | a >> 30;
+    d[0] = (a & 0x0F00F00Fu) | (t & 0xC03C03C0u);
+    d[1] = (b & 0xF00F00F0u) | (w & 0x03C03C03u);
+    d[2] = (a & 0x00F00F00u) | (w & 0x3C03C03Cu);
 }
 
 // Weights of the global-fed kernel (internal.h): row r of row tile i of
@@ -103,14 +105,23 @@ int e2m3_channel(int p)
 // holds consecutive channels of its pixel); chunk g of K step ks is chunk
 // 4 ks + g of the window, taps in order; chunks past the window are zeros.
 // wv: decoded values [cout][taps][cin].
-std::vector<uint8_t> gf_weights(int kind, int cout, int taps, int cin, int groups, int steps, const int16_t *wv)
+// packed: the same weights as 4-bit fields (else null), value: what a field decodes to.
+std::vector<uint8_t> gf_weights(int kind, int cout, int taps, int cin, int groups, int steps, const int16_t *wv,
+                                const uint8_t *packed, const int16_t *value)
 {
+    uint8_t mag[256], sgn[256];   // per byte of two fields: magnitudes, 2 where negative
+    if (packed)
+        for (int b = 0; b < 256; ++b) {
+            const int lo = value[b & 15], hi = value[b >> 4];
+            mag[b] = (uint8_t)((lo < 0 ? -lo : lo) | (hi < 0 ? -hi : hi) << 4);
+            sgn[b] = (uint8_t)((lo < 0 ? 2 : 0) | (hi < 0 ? 32 : 0));
+        }
     const int ch = kind == GF_I8 ? 16 : 32, chunks = taps * (cin / ch);
     const size_t tile = kind == GF_F6 ? GF_F6_TILE : 1024;
     std::vector<uint8_t> out((size_t)groups * steps * 4 * tile, 0);
     int order[32];
     for (int p = 0; p < ch; ++p)
-        order[p] = kind == GF_F6 ? e2m3_channel(p) : kind == GF_F4 ? fp4_channel(p) : p;
+        order[p] = kind == GF_F4 ? fp4_channel(p) : p;
     for (int co = 0; co < cout; ++co) {
         const int ct = co / 64, i = co % 16 / 4, r = 4 * (co % 64 / 16) + co % 4;
         // (the chunks of a channel's taps are consecutive: cin is a multiple of ch)
@@ -119,21 +130,31 @@ std::vector<uint8_t> gf_weights(int kind, int cout, int taps, int cin, int group
             uint8_t *t = out.data() + (((size_t)ct * steps + kc / 4) * 4 + i) * tile;
             const int lane = 16 * (kc % 4) + r;
             if (kind == GF_F6) {
-                // e2m3 of w / 8: sign and magnitude, |w| <= 15; 16 fields of 6 bits
-                // per three words
+                // e2m3 of w / 8, |w| <= 15: sign and magnitude in 6-bit fields. The
+                // magnitudes as packed nibbles go through the kernel's own widening,
+                // and so do the signs, four bits up (bit 5 of a field = bit 1 of the
+                // nibble)
                 uint32_t w[6];
                 for (int h = 0; h < 2; ++h) {
-                    uint64_t f[16];
-                    for (int p = 0; p < 16; ++p) {
-                        const int v = src[order[16 * h + p]];
-                        f[p] = v < 0 ? 32u - v : v;
+                    uint32_t m[2] = {0, 0}, sg[2] = {0, 0};
+                    if (packed) {
+                        const uint8_t *f = packed + ((size_t)co * taps * cin + (size_t)kc * ch + 16 * h) / 2;
+                        for (int c = 0; c < 8; ++c) {
+                            m[c / 4] |= (uint32_t)mag[f[c]] << (8 * (c % 4));
+                            sg[c / 4] |= (uint32_t)sgn[f[c]] << (8 * (c % 4));
+                        }
                     }
-                    const uint64_t lo = f[0] | f[1] << 6 | f[2] << 12 | f[3] << 18 | f[4] << 24 | f[5] << 30 |
-                                        f[6] << 36 | f[7] << 42 | f[8] << 48 | f[9] << 54 | f[10] << 60;
-                    w[3 * h] = (uint32_t)lo;
-                    w[3 * h + 1] = (uint32_t)(lo >> 32);
-                    w[3 * h + 2] = (uint32_t)(f[10] >> 4 | f[11] << 2 | f[12] << 8 | f[13] << 14 | f[14] << 20 |
-                                              f[15] << 26);
+                    for (int c = 0; c < 16 && !packed; ++c) {
+                        const int v = src[16 * h + c], neg = v < 0;
+                        m[c / 8] |= (uint32_t)(neg ? -v : v) << (4 * (c % 8));
+                        sg[c / 8] |= (uint32_t)(neg ? 2 : 0) << (4 * (c % 8));
+                    }
+                    uint32_t a[3], b[3];
+                    host_spread6(m[0], m[1], a);
+                    host_spread6(sg[0], sg[1], b);
+                    w[3 * h] = a[0] | b[0] << 4;
+                    w[3 * h + 1] = a[1] | b[1] << 4 | b[0] >> 28;
+                    w[3 * h + 2] = a[2] | b[2] << 4 | b[1] >> 28;
                 }
                 std::memcpy(t + 16 * lane, w, 16);
                 std::memcpy(t + 1024 + 8 * lane, w + 4, 8);
@@ -489,7 +510,8 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
         const int chunk = h.gf_kind == GF_I8 ? 16 : 32;
         h.gf_groups = (d.cout + 63) / 64;
         h.gf_steps = (taps * (d.cin / chunk) + 3) / 4;
-        gfw = gf_weights(h.gf_kind, d.cout, taps, d.cin, h.gf_groups, h.gf_steps, wv.data());
+        gfw = gf_weights(h.gf_kind, d.cout, taps, d.cin, h.gf_groups, h.gf_steps, wv.data(),
+                         d.bits_w == 4 ? w_packed : nullptr, value);
         const int pad = 64 * h.gf_groups;
         gfe.assign((size_t)d.num_levels * EPI_FIELDS * pad, 0);
         for (int l = 0; l < d.num_levels && h.gf_kind != GF_NONE; ++l)
@@ -519,29 +541,41 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     qconv_s *hp = new (std::nothrow) qconv_s(h);
     if (!hp)
         return fail(AQD_ERR_NOMEM, "host allocation failed");
-    // one device allocation and copy for the weights, the tables and the skip
-    // tables (256-byte aligned parts). MFMA weights: four K steps of 256-row tiles
+    // one device allocation for the weights, the tables and the skip tables
+    // (256-byte aligned parts). MFMA weights: four K steps of 256-row tiles
     // (64 KiB) of padding past the end, which the register-fed kernel's
     // look-ahead may read (never use)
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t o_epi = up(wbuf.size() + (mfma ? 4 * 256 * KC : 0)), o_lut = o_epi + up(epi.size() * sizeof(int32_t)),
                  o_gfw = o_lut + up(lut.size() * sizeof(int32_t)), o_gfe = o_gfw + up(gfw.size()),
                  total = o_gfe + gfe.size() * sizeof(int32_t);
-    std::vector<uint8_t> blob(total, 0);
-    auto put = [&](size_t at, const void *src, size_t n) {
-        if (n)
-            std::memcpy(blob.data() + at, src, n);
-    };
-    put(0, wbuf.data(), wbuf.size());
-    put(o_epi, epi.data(), epi.size() * sizeof(int32_t));
-    put(o_lut, lut.data(), lut.size() * sizeof(int32_t));
-    put(o_gfw, gfw.data(), gfw.size());
-    put(o_gfe, gfe.data(), gfe.size() * sizeof(int32_t));
     if (hipMalloc(&hp->w_dev, total) != hipSuccess) {
         delete hp;
         return fail(AQD_ERR_NOMEM, "hipMalloc of the weights and tables failed");
     }
-    if (hipMemcpy(hp->w_dev, blob.data(), total, hipMemcpyHostToDevice) != hipSuccess) {
+    struct Part {
+        size_t at;
+        const void *src;
+        size_t n;
+    };
+    const Part parts[5] = {{0, wbuf.data(), wbuf.size()},
+                           {o_epi, epi.data(), epi.size() * sizeof(int32_t)},
+                           {o_lut, lut.data(), lut.size() * sizeof(int32_t)},
+                           {o_gfw, gfw.data(), gfw.size()},
+                           {o_gfe, gfe.data(), gfe.size() * sizeof(int32_t)}};
+    bool copied = true;
+    if (total <= (256u << 10)) {   // small: one copy
+        std::vector<uint8_t> blob(total, 0);
+        for (const Part &q : parts)
+            if (q.n)
+                std::memcpy(blob.data() + q.at, q.src, q.n);
+        copied = hipMemcpy(hp->w_dev, blob.data(), total, hipMemcpyHostToDevice) == hipSuccess;
+    } else {
+        for (const Part &q : parts)
+            copied = copied && (!q.n || hipMemcpy((uint8_t *)hp->w_dev + q.at, q.src, q.n, hipMemcpyHostToDevice) ==
+                                            hipSuccess);
+    }
+    if (!copied) {
         (void)hipFree(hp->w_dev);
         delete hp;
         return fail(AQD_ERR_DEVICE, "copy of the weights to the device failed");
@@ -877,7 +911,16 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
 // (own: its tile, -1: the direct kernel). t64 counts tiles of 64 x 64 outputs,
 // steps K steps of 128 channels (64 of 8-bit codes). Measured on MI355X, us per
 // launch in a graph of 20, own -> new (P pixels; "gf n" n waves, "fx a x b" tiles):
-//  * t64 <= 512 (two tiles per CU): gf. 3x3 256 -> 256 P 4200 27.6 -> 11.3; 1x1 2048
+//  * 3x3, stride 1, 64, 128 or a multiple of 256 channels in: fx3 from t64 200 on, 512 with
+//    256 channels or more (256 -> 256 P 4200, t64 264: fx3 10.3, gf 11.3 on weights in the
+//    L2, but in a network, where they are not, 15 and 12; 512 -> 512 P 1050: 16.0 and 10.6).
+//    64 -> 64 P 534400 37.7 -> 27.1; 128 -> 128 P 133600 31.2 -> 21.2, with a skip 42.7 ->
+//    26.0; 256 -> 256 P 33600 23.0 -> 20.6, P 133600 78 -> 55, P 267200 139 -> 94; 256 ->
+//    720 int32 P 133600 235 -> 164; 512 -> 512 P 8400 39.7 -> 24.7. At 256 channels in and
+//    up to 64 out gf stays up to t64 1100 (256 -> 36 P 66800: 23.1, fx3 26.1). 256 x 128
+//    tiles where the tiles still fill the chip (P 16700: 14.3, 256 x 64 15.5; 256 -> 720 P
+//    4200: 17.4, 13.0), at 2 bits 128 x 128 up to larger sizes (P 133600: 44.2, 42.0);
+//  * else t64 <= 512 (two tiles per CU): gf. 3x3 256 -> 256 P 4200 27.6 -> 11.3; 1x1 2048
 //    -> 512 P 1050 21 -> 7.4; 3x3 stride 2 2048 -> 256 P 273 30 -> 21, P 2184 37 -> 29;
 //    3x3 64 -> 64 P 1024 14.9 -> 4.6. So do the shapes of the direct kernel, at any
 //    size (3x3 256 -> 1 P 44600 1470 -> 8);
@@ -908,37 +951,56 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
     const bool f4 = h0.gf_kind == GF_F4, codes = h0.d.out_mode == AQD_OUT_CODES, mfma = own >= 0;
     long long t64 = 0;
     for (int i = 0; i < count; ++i) {
-        if (segs[i].conv->gf_kind != h0.gf_kind || chk[i].xbytes >= (1ull << 31))
-            return false;
-        t64 += ((long long)segs[i].n * chk[i].ho * chk[i].wo + 63) / 64 * h0.gf_groups;
+        const long long P = (long long)segs[i].n * chk[i].ho * chk[i].wo;
+        if (segs[i].conv->gf_kind != h0.gf_kind || chk[i].xbytes >= (1ull << 31) || P + 256 >= (1LL << 31))
+            return false;   // (32-bit buffer offsets and pixel numbers)
+        t64 += (P + 63) / 64 * h0.gf_groups;
     }
     const bool narrow = h0.tile_cfg == TILE_128x256 || h0.tile_cfg == TILE_64x512;
-    bool gf = !mfma || t64 <= 512;
-    if (!gf && f4)
-        gf = h0.d.skip_bits == 32 || (cout <= 64 && (codes || t64 <= 1100)) || (cout <= 128 && t64 <= 1100);
-    else if (!gf && h0.gf_kind == GF_F6)
-        gf = narrow && steps > 2 && t64 <= 1100;
-    // waves along channels and column tiles of the tiled kernel
-    int wc = 0, nj = 4;
-    if (!gf && h0.gf_kind != GF_I8 &&
-        (codes ? cout % 16 == 0 && h0.d.bits_out == h0.d.bits_in && h0.d.skip_bits != 32 &&
-                     (h0.d.skip_bits == 0 || h0.d.skip_bits == h0.d.bits_in)
-               : cout % 4 == 0)) {
-        if (f4 && cout > 64 && !(h0.d.cin == 64 && h0.d.kh == 1 && t64 > 8000)) {
-            wc = cout <= 128 ? 2 : 4;
-            nj = wc == 4 && t64 > (codes ? 12000 : 4000) ? 8 : 4;
-        } else if (!f4 && narrow && cout > 64 && steps >= 9 && (!codes || t64 <= 1500)) {
-            wc = 2;
-        } else if (!f4 && !narrow && own != TILE_WV144 &&
-                   (steps >= 9 || (steps == 8 && t64 <= 1100 && h0.d.skip_bits == 0))) {
+    // waves along channels and column tiles of the tiled kernels; kw 0: fx, -1: fx3
+    int wc = 0, nj = 4, kw = 0;
+    const bool tiled = h0.gf_kind != GF_I8 &&
+                       (codes ? cout % 16 == 0 && h0.d.bits_out == h0.d.bits_in &&
+                                    (h0.d.skip_bits == 0 || h0.d.skip_bits == h0.d.bits_in)
+                              : cout % 4 == 0);
+    const bool skip = h0.d.skip_bits != 0;
+    const int cin = h0.d.cin;
+    bool gf = false;
+    if (tiled && t64 > (cin >= 256 ? 512 : 200) && h0.d.kh == 3 && h0.d.kw == 3 && h0.d.stride == 1 && h0.d.pad == 1 &&
+        (cin == 64 || cin == 128 || cin % 256 == 0) && !(cin >= 256 && cout <= 64 && t64 <= 1100)) {
+        kw = -1;
+        if (cin == 64)
+            wc = 1;
+        else if (cin > 256)
             wc = 4;
-            nj = t64 > 1024 && h0.d.skip_bits == 0 ? 8 : 4;
+        else if (cin == 128 || cout <= 128)
+            wc = 2;
+        else if (f4) {
+            wc = !skip && t64 > (codes ? 15000 : 2500) ? 4 : 2;
+            nj = wc == 4 ? 8 : 4;
+        } else {
+            wc = skip && t64 <= 1500 ? 2 : 4;
+            nj = !skip && t64 > 1000 ? 8 : 4;
         }
-    }
-    if (!gf && !wc)
+    } else if (!mfma || t64 <= 512) {
+        gf = true;
+    } else if (f4 && (h0.d.skip_bits == 32 || (cout <= 64 && (codes || t64 <= 1100)) || (cout <= 128 && t64 <= 1100))) {
+        gf = true;
+    } else if (h0.gf_kind == GF_F6 && narrow && steps > 2 && t64 <= 1100) {
+        gf = true;
+    } else if (tiled && f4 && cout > 64 && !(cin == 64 && h0.d.kh == 1 && t64 > 8000)) {
+        wc = cout <= 128 ? 2 : 4;
+        nj = wc == 4 && t64 > (codes ? 12000 : 4000) ? 8 : 4;
+    } else if (tiled && !f4 && narrow && cout > 64 && steps >= 9 && (!codes || t64 <= 1500)) {
+        wc = 2;
+    } else if (tiled && !f4 && !narrow && own != TILE_WV144 && (steps >= 9 || (steps == 8 && t64 <= 1100 && !skip))) {
+        wc = 4;
+        nj = t64 > 1024 && !skip ? 8 : 4;
+    } else {
         return false;
-    if (wc)
-        *plan = GfPlan{h0.gf_kind, wc, nj, 0};
+    }
+    if (!gf)
+        *plan = GfPlan{h0.gf_kind, wc, nj, kw};
     else {
         // the waves of a tile split its K range while there are too few tiles to
         // give every SIMD two waves; very few tiles are halved as well. 3x3 128 ->
@@ -979,7 +1041,8 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
         m.side0 = s.conv->side0[s.level];
         m.lut = s.conv->lut_dev ? s.conv->lut_dev + (size_t)s.level * s.conv->cout_pad * (1 << h0.d.skip_bits)
                                 : nullptr;
-        tiles += (m.P + px - 1) / px * groups;
+        const long long vp = plan->kw < 0 ? (long long)s.n * (s.h + 1) * (s.w + 1) : m.P;  // virtual pixels
+        tiles += (vp + px - 1) / px * groups;
         if (tiles >= (1LL << 26))
             return false;
     }
@@ -1004,7 +1067,7 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
 
 hipError_t launch_gf(const MfmaArgs &a, const GfPlan &p, hipStream_t stream)
 {
-    return p.kw == 0 ? launch_qconv_fx(a, p, stream) : launch_qconv_gf(a, p, stream);
+    return p.kw <= 0 ? launch_qconv_fx(a, p, stream) : launch_qconv_gf(a, p, stream);
 }
 
 // Split of the K range: the number of parts minimising a simple model of the

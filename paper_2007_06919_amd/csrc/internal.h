@@ -131,7 +131,7 @@ struct GfPlan {
 // a.co_tiles counts workgroup tiles (4 / mi per 64-channel group), a.ksteps
 // steps of four chunks (32 channels, or 16 of 8-bit codes); the segments' wt and
 // epi are the stored gf weights and tables (cout_pad a multiple of 64)
-// (qconv_fx.hip: kw = 0, mi = waves along channels (64 channels each), nj =
+// (qconv_fx.hip: kw = 0, or -1 for the 3x3 stride 1 kernel; mi = waves along channels (64 channels each), nj =
 // column tiles per wave; a.co_tiles counts tiles of 64 mi channels; seg.lut and
 // seg.side0 as for the other kernels)
 hipError_t launch_qconv_fx(const MfmaArgs &a, const GfPlan &p, hipStream_t stream);

@@ -54,9 +54,8 @@ __device__ __forceinline__ uint2 load_b64(buf_rsrc r, int voff, int soff)
 // 16 codes of 4 bits (words a, b) -> 16 e2m3 values in 6-bit fields (three
 // words): the field of a code is the code itself, zero extended (code / 8 in
 // e2m3), so each code moves to a field at a multiple of 6 bits. The codes keep
-// the offset they have modulo 4 or move up by 2, which takes them in the order
-// e2m3_channel (aqd_api.hip; the weights were stored in that order): 8
-// instructions for 16 codes.
+// the offset they have modulo 4 or move up by 2, in an order of their own (the
+// weights were widened the same way at create): 8 instructions for 16 codes.
 __device__ __forceinline__ void spread6(uint32_t a, uint32_t b, int &d0, int &d1, int &d2)
 {
     const uint32_t t = a << 2, w = __builtin_amdgcn_alignbit(b, a, 30);  // w = b << 2 | a >> 30

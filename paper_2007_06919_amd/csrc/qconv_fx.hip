@@ -41,6 +41,221 @@ namespace {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+// LDS bytes the epilogue needs
+template <int KIND, int WC, int NJ, int OUTK, int SKK>
+constexpr int fx_epilogue_bytes()
+{
+    constexpr int BPX = 16 * NJ * (4 / WC), BO = KIND == GF_F6 ? 4 : 2;
+    constexpr int tabs = WC * (EPI_FIELDS + (SKK == 1 ? 1 << BO : 0)) * 64 * 4;
+    constexpr int outb = OUTK == 1 ? 64 * WC * 64 * 4 : BPX * WC * 64 * BO / 8;
+    return OUTK == 1 || outb > tabs ? outb : tabs;
+}
+
+// The epilogue of both tiled kernels: accumulators -> outputs. pixel(p): output
+// pixel of the tile's pixel p (wave wp's column j: pixels 16 (NJ wp + j) + r), or
+// -1. lds: fx_epilogue_bytes, free once every wave has arrived here.
+template <int KIND, int WC, int NJ, int OUTK, int SKK, int FAST, typename PX>
+__device__ __forceinline__ void fx_epilogue(const MfmaArgs &A, const MfmaSeg &S, uint8_t *lds, v4f (&acc)[4][NJ],
+                                            const int co_tile, const int tid, PX &&pixel)
+{
+    constexpr bool F6 = KIND == GF_F6;
+    constexpr int MI = 4, BPX = 16 * NJ * (4 / WC);
+    constexpr int BO = F6 ? 4 : 2, QMAX = (1 << BO) - 1;   // output code width
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wc = wave % WC, wp = wave / WC, r = lane & 15, g = lane >> 4;
+    const int pw = 16 * NJ * wp + r;
+    const int ct = co_tile * WC + wc, groups = A.cout_pad / 64, hw = S.ho * S.wo;
+    constexpr float UNIT = F6 ? 64.f : 2.f;
+    const int c0 = 64 * ct + 16 * g;                 // first of this lane's 16 channels
+    if constexpr (OUTK == 1) {
+        // int32 outputs, 64 pixels of the tile at a time: each lane's 16 channels
+        // go to LDS rows of WC * 64 int32 (16-byte chunk c of pixel p at
+        // c ^ (p & 7)), then every thread stores 16-byte chunks of whole rows
+        constexpr int CH = WC * 16;                  // chunks per row
+        v4i bias[MI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+            bias[i] = ct < groups ? *(const v4i *)(S.epi + EPI_BIAS * A.cout_pad + c0 + 4 * i) : v4i{0, 0, 0, 0};
+        const int valid = min(A.cout - co_tile * (WC * 64), WC * 64) / 4;
+        static_for<BPX / 64>([&](auto pc) {
+            constexpr int pass = decltype(pc)::value;
+            __syncthreads();   // the ring, or the last pass's rows, are no longer read
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                // this wave's column j is pixels 16 (NJ wp + j) .. of the tile
+                if ((NJ * wp + j) / 4 == pass) {
+                    const int p = (16 * (NJ * wp + j)) % 64 + r;
+#pragma unroll
+                    for (int i = 0; i < MI; ++i) {
+                        const int c = 16 * wc + 4 * g + i;
+                        const v4f a = acc[i][j];
+                        *(v4i *)(lds + (p * CH + (c ^ (p & 7))) * 16) =
+                            v4i{(int)(a.x * UNIT), (int)(a.y * UNIT), (int)(a.z * UNIT), (int)(a.w * UNIT)} + bias[i];
+                    }
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int it = 0; it < CH / 4; ++it) {
+                const int idx = it * 256 + tid;
+                const int p = idx / CH, c = idx % CH;
+                const long long px = pixel(64 * pass + p);
+                if (px >= 0 && c < valid)
+                    *(v4i *)((int32_t *)S.y + px * A.cout + co_tile * (WC * 64) + 4 * c) =
+                        *(const v4i *)(lds + (p * CH + (c ^ (p & 7))) * 16);
+            }
+        });
+        return;
+    }
+
+    // ---------------------------------------------------------------- epilogue
+    constexpr int OW = BO / 2;                       // words of a lane's 16 channels
+    const bool co_ok = c0 < A.cout;                  // (cout is a multiple of 16: all 16 or none)
+    uint32_t skw[NJ][OW];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+#pragma unroll
+        for (int o = 0; o < OW; ++o)
+            skw[j][o] = 0;
+        if constexpr (SKK == 1) {
+            const long long px = pixel(pw + 16 * j);
+            if (co_ok && px >= 0) {
+                long long spix = px;
+                if (A.up2) {
+                    const unsigned pn = (unsigned)px / (unsigned)hw, prem = (unsigned)px - pn * (unsigned)hw;
+                    const unsigned oh = prem / (unsigned)S.wo, ow = prem - oh * (unsigned)S.wo;
+                    spix = ((long long)pn * S.hs + (oh >> 1)) * S.ws + (ow >> 1);
+                }
+                const uint8_t *src = (const uint8_t *)S.skip + (spix * A.cout + c0) * BO / 8;
+                load_words<OW>(src, skw[j]);
+            }
+        }
+    }
+    __syncthreads();   // every wave is done with the ring
+    // the tables of the tile's channels, and of side-0 skips RSM(k, c, d) per code
+    int32_t *prm = (int32_t *)lds;                   // [EPI_FIELDS][WC * 64]
+    int32_t *lut = prm + EPI_FIELDS * WC * 64;       // [WC * 64][QMAX + 1]
+    const bool use_lut = SKK == 1 && S.side0;
+    for (int u = tid; u < EPI_FIELDS * WC * 64; u += 256) {
+        const int f = u / (WC * 64), c = u % (WC * 64);
+        prm[u] = co_tile * (WC * 64) + c < A.cout_pad ? S.epi[f * A.cout_pad + co_tile * (WC * 64) + c] : 0;
+    }
+    if (use_lut)
+        for (int u = tid; u < WC * 64 * (QMAX + 1); u += 256)
+            lut[u] = co_tile * (WC * 64) + u / (QMAX + 1) < A.cout
+                         ? S.lut[(long long)co_tile * (WC * 64) * (QMAX + 1) + u] : 0;
+    __syncthreads();
+    uint32_t outw[NJ][OW];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int o = 0; o < OW; ++o)
+            outw[j][o] = 0;
+    const int cl = 64 * wc + 16 * g;
+    const int32_t *lut_l = lut + cl * (QMAX + 1);
+    auto group = [&](auto lut_c, auto ic) {
+        constexpr bool LUT = decltype(lut_c)::value;
+        constexpr int i = decltype(ic)::value;
+        const int32_t *tab = prm + cl + 4 * i;
+        const v4i bias = *(const v4i *)(tab + EPI_BIAS * WC * 64);
+        const v4i mult = *(const v4i *)(tab + EPI_MULT * WC * 64);
+        const v4i shf = *(const v4i *)(tab + (FAST ? EPI_SHR : EPI_SHIFT) * WC * 64);
+        v4i rnd = {0, 0, 0, 0}, sc = rnd, sd = rnd, ss = rnd;
+        if constexpr (FAST)
+            rnd = *(const v4i *)(tab + EPI_RND * WC * 64);
+        long long srnd[4] = {0, 0, 0, 0};
+        if constexpr (SKK != 0 && !LUT) {
+            sc = *(const v4i *)(tab + EPI_SKIP_C * WC * 64);
+            sd = *(const v4i *)(tab + EPI_SKIP_D * WC * 64);
+            ss = *(const v4i *)(tab + EPI_SKIP_SIDE * WC * 64);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                srnd[e] = rsm_rnd(sd[e]);
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int v = (int)(acc[i][j][e] * UNIT) + bias[e];
+                const int bit = (4 * i + e) * BO;
+                int kv = 0;
+                if constexpr (SKK == 1)
+                    kv = (int)__builtin_amdgcn_ubfe(skw[j][bit >> 5], bit & 31, BO);
+                int y;
+                if constexpr (FAST) {
+                    int u = v;
+                    if constexpr (LUT) {
+                        u = (int)((unsigned)v + (unsigned)lut_l[(4 * i + e) * (QMAX + 1) + kv]);
+                    } else if constexpr (SKK != 0) {
+                        const int scaled = rsm32r(ss[e] ? v : kv, sc[e], srnd[e], sd[e]);
+                        u = (int)((unsigned)scaled + (unsigned)(ss[e] ? kv : v));
+                    }
+                    y = requant32(u, mult[e], (long long)rnd[e] << 32, shf[e]);
+                    y = y < 0 ? 0 : (y > QMAX ? QMAX : y);
+                } else {
+                    long long u = v;
+                    if constexpr (LUT)
+                        u = (int)((unsigned)v + (unsigned)lut_l[(4 * i + e) * (QMAX + 1) + kv]);
+                    else if constexpr (SKK != 0)
+                        u = align_add(v, kv, sc[e], sd[e], ss[e]);
+                    y = (int)requant_clamp(u, mult[e], shf[e], QMAX);
+                    asm volatile("" : "+v"(y));   // one 64-bit product alive at a time
+                }
+                outw[j][bit >> 5] |= (uint32_t)y << (bit & 31);
+            }
+        }
+    };
+    if (use_lut)
+        static_for<MI>([&](auto ic) { group(std::true_type{}, ic); });
+    else
+        static_for<MI>([&](auto ic) { group(std::false_type{}, ic); });
+    if (F6 && A.qmax == 7) {   // 3-bit codes (clamped to 15 above)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int o = 0; o < OW; ++o)
+                outw[j][o] = sat7_nibbles(outw[j][o]);
+    }
+    // the packed words are complete here (see the fences of the other kernels)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int o = 0; o < OW; ++o)
+            asm volatile("" : "+v"(outw[j][o]));
+    // a whole channel tile's codes go through LDS and out as 16-byte chunks of
+    // contiguous pixel rows; a partial one is stored from registers
+    constexpr int ROWB = WC * 64 * BO / 8, CPR = ROWB / 16;
+    if (A.cout - co_tile * (WC * 64) >= WC * 64) {
+        __syncthreads();
+        const int cb = cl * BO / 8;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int p = pw + 16 * j;
+            uint8_t *d = lds + p * ROWB + 16 * ((cb >> 4) ^ (p & (CPR - 1))) + (cb & 15);
+            store_words<OW>(d, outw[j]);
+        }
+        __syncthreads();
+        const long long rowg = (long long)A.cout * BO / 8;
+#pragma unroll
+        for (int it = 0; it < (BPX * CPR + 255) / 256; ++it) {
+            const int idx = it * 256 + tid;
+            const int p = idx / CPR, c = idx % CPR;
+            const long long px = p < BPX ? pixel(p) : -1;
+            if (px >= 0)
+                *(uint4 *)((uint8_t *)S.y + px * rowg + co_tile * ROWB + 16 * c) =
+                    *(const uint4 *)(lds + p * ROWB + 16 * (c ^ (p & (CPR - 1))));
+        }
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const long long px = pixel(pw + 16 * j);
+        if (co_ok && px >= 0)
+            store_words<OW>((uint8_t *)S.y + (px * A.cout + c0) * BO / 8, outw[j]);
+    }
+}
+
+
 // OUTK: 0 = codes of the input's width, 1 = int32; SKK: 0 = none, 1 = codes of
 // the input's width; FAST: every shift >= 2 (32-bit requantisation); OCC:
 // workgroups per CU
@@ -56,10 +271,7 @@ __global__ void __launch_bounds__(256, OCC) qconv_fx_kernel(MfmaArgs A)
     constexpr int WB = F6 ? GF_F6_TILE : 1024;       // weight bytes of a row tile and K step
     constexpr int XROW = 128, YROW = F6 ? 64 : 0;    // LDS bytes of a pixel and stage
     constexpr int STAGE = BPX * (XROW + YROW);
-    constexpr int BO = F6 ? 4 : 2, QMAX = (1 << BO) - 1;   // output code width
-    constexpr int TABS = WC * (EPI_FIELDS + (SKK == 1 ? QMAX + 1 : 0)) * 64 * 4;
-    constexpr int OUTB = OUTK == 1 ? 64 * WC * 64 * 4 : BPX * WC * 64 * BO / 8;
-    constexpr int EPIB = OUTK == 1 ? OUTB : TABS > OUTB ? TABS : OUTB;
+    constexpr int EPIB = fx_epilogue_bytes<KIND, WC, NJ, OUTK, SKK>();
     constexpr int LDS = 2 * STAGE > EPIB ? 2 * STAGE : EPIB;
     constexpr int RA = NJ >= 8 ? 2 : 1;              // fragments are read RA column tiles ahead
     static_assert(NJ >= 4 && NPC >= 2 && NPC <= 8, "tile");
@@ -199,11 +411,11 @@ __global__ void __launch_bounds__(256, OCC) qconv_fx_kernel(MfmaArgs A)
     };
     auto load_w = [&](int k, int i) -> Wt {
         Wt w;
-        const int ko = min(k, KS) * (4 * WB);        // a step past the last: at the buffer's end, zeros
-        w.x = load_b128(wr, lane * 16 + i * WB, ko);
+        const int ko = min(k, KS) * (4 * WB) + i * WB;   // a step past the last: past the buffer's end
+        w.x = load_b128(wr, lane * 16, ko);
         w.y = make_uint2(0, 0);
         if constexpr (F6)
-            w.y = load_b64(wr, lane * 8 + i * WB + 1024, ko);
+            w.y = load_b64(wr, lane * 8, ko + 1024);
         return w;
     };
 
@@ -288,193 +500,265 @@ __global__ void __launch_bounds__(256, OCC) qconv_fx_kernel(MfmaArgs A)
         buf ^= STAGE;
     }
 
-    constexpr float UNIT = F6 ? 64.f : 2.f;
-    const int c0 = 64 * ct + 16 * g;                 // first of this lane's 16 channels
-    const long long pxw = (long long)px_tile * BPX + pw;
-    if constexpr (OUTK == 1) {
-        // int32 outputs, 64 pixels of the tile at a time: each lane's 16 channels
-        // go to LDS rows of WC * 64 int32 (16-byte chunk c of pixel p at
-        // c ^ (p & 7)), then every thread stores 16-byte chunks of whole rows
-        constexpr int CH = WC * 16;                  // chunks per row
-        v4i bias[MI];
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-            bias[i] = ct < groups ? *(const v4i *)(S.epi + EPI_BIAS * A.cout_pad + c0 + 4 * i) : v4i{0, 0, 0, 0};
-        const int valid = min(A.cout - co_tile * (WC * 64), WC * 64) / 4;
-        static_for<BPX / 64>([&](auto pc) {
-            constexpr int pass = decltype(pc)::value;
-            __syncthreads();   // the ring, or the last pass's rows, are no longer read
-#pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                // this wave's column j is pixels 16 (NJ wp + j) .. of the tile
-                if ((NJ * wp + j) / 4 == pass) {
-                    const int p = (16 * (NJ * wp + j)) % 64 + r;
-#pragma unroll
-                    for (int i = 0; i < MI; ++i) {
-                        const int c = 16 * wc + 4 * g + i;
-                        const v4f a = acc[i][j];
-                        *(v4i *)(lds + (p * CH + (c ^ (p & 7))) * 16) =
-                            v4i{(int)(a.x * UNIT), (int)(a.y * UNIT), (int)(a.z * UNIT), (int)(a.w * UNIT)} + bias[i];
-                    }
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int it = 0; it < CH / 4; ++it) {
-                const int idx = it * 256 + tid;
-                const int p = idx / CH, c = idx % CH;
-                const long long px = (long long)px_tile * BPX + 64 * pass + p;
-                if (px < S.P && c < valid)
-                    *(v4i *)((int32_t *)S.y + px * A.cout + co_tile * (WC * 64) + 4 * c) =
-                        *(const v4i *)(lds + (p * CH + (c ^ (p & 7))) * 16);
-            }
-        });
-        return;
-    }
+    fx_epilogue<KIND, WC, NJ, OUTK, SKK, FAST>(A, S, lds, acc, co_tile, tid, [&](int p) -> long long {
+        const long long px = (long long)px_tile * BPX + p;
+        return px < S.P ? px : -1;
+    });
+}
 
-    // ---------------------------------------------------------------- epilogue
-    constexpr int OW = BO / 2;                       // words of a lane's 16 channels
-    const bool co_ok = c0 < A.cout;                  // (cout is a multiple of 16: all 16 or none)
-    uint32_t skw[NJ][OW];
+// 3x3, stride 1, pad 1 convolutions with the input tile kept in LDS for all nine
+// taps: a block of 32 CB input channels of every pixel that the tile's windows
+// touch is widened into LDS once, and the K steps of the nine taps then run with
+// neither copies nor barriers, reading their fragments at shifted pixels (the
+// tiled kernel above widens each pixel up to nine times, and waits once per stage).
+//
+// The tile's BPX pixels are consecutive in a virtual image that stands in for the
+// padding: rows of W + 1 (the extra pixel is the right pad of its row and the left
+// pad of the next), H + 1 rows per image (the extra row is the bottom pad of its
+// image and the top pad of the next). A window then is three runs of BPX + 2
+// consecutive virtual pixels, W + 1 apart, whatever rows and images it spans, and a
+// tile loses only the virtual pixels it holds (2% at 100 x 167).
+//
+// 3x3 256 -> 256 on 267200 pixels: 107 us on the kernel above, 94 here (140 on the
+// int8 kernel); 128 -> 128 on 133600: 30.5 -> 21.2; 2 bits 21.6 -> 18.1.
+//
+// Weights one K step ahead in registers, activation fragments RA column tiles
+// ahead. Input channels beyond a block (256, or 128 for layers of 128): block after
+// block, two barriers each.
+// MULTI: more than one block (else cin is the block's)
+template <int KIND, int WC, int NJ, int OUTK, int SKK, int FAST, int CB, int MULTI>
+__global__ void __launch_bounds__(256, 2) qconv_fx3_kernel(MfmaArgs A)
+{
+    constexpr bool F6 = KIND == GF_F6;
+    constexpr int WP = 4 / WC, MI = 4;
+    constexpr int Q = CB == 8 ? 2 : 1;               // K steps per tap and block (CB 2: per pair of taps)
+    constexpr int BPX = 16 * NJ * WP, RUN = BPX + 2, NPX = 3 * RUN;
+    constexpr int XB = F6 ? 16 : 8;                  // packed bytes of a chunk
+    constexpr int WB = F6 ? GF_F6_TILE : 1024;       // weight bytes of a row tile and K step
+    constexpr int XROW = 16 * CB, YROW = F6 ? 8 * CB : 0;
+    constexpr int TAB = (NPX * 4 + 127) / 128 * 128;
+    constexpr int DATA = NPX * (XROW + YROW);
+    constexpr int EPIB = fx_epilogue_bytes<KIND, WC, NJ, OUTK, SKK>();
+    constexpr int LDS = TAB + (DATA > EPIB ? DATA : EPIB);
+    constexpr int PPI = 256 / CB, IT = (NPX + PPI - 1) / PPI;   // pixels per copy pass, passes
+    constexpr int RA = NJ >= 8 ? 2 : 1;
+    static_assert(CB == 8 || CB == 4 || CB == 2, "chunks per block");
+    static_assert(CB == 8 || !MULTI, "blocks of 8 chunks");
+    __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS];
+    int *const tab = (int *)lds;                     // input pixel of virtual pixel i of run t, or -1
+    uint8_t *const data = lds + TAB;
+
+    const int bid = blockIdx.x;
+    const int tile = (bid & 7) * A.tiles_per_xcd + (bid >> 3);
+    if (tile >= A.total_tiles)
+        return;
+    int s = 0;
+    if (A.nseg > 1) {
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-#pragma unroll
-        for (int o = 0; o < OW; ++o)
-            skw[j][o] = 0;
-        if constexpr (SKK == 1) {
-            const long long px = pxw + 16 * j;
-            if (co_ok && px < S.P) {
-                long long spix = px;
-                if (A.up2) {
-                    const unsigned pn = (unsigned)px / (unsigned)hw, prem = (unsigned)px - pn * (unsigned)hw;
-                    const unsigned oh = prem / (unsigned)S.wo, ow = prem - oh * (unsigned)S.wo;
-                    spix = ((long long)pn * S.hs + (oh >> 1)) * S.ws + (ow >> 1);
-                }
-                const uint8_t *src = (const uint8_t *)S.skip + (spix * A.cout + c0) * BO / 8;
-                load_words<OW>(src, skw[j]);
-            }
+        for (int i = 1; i < AQD_MAX_SEGS; ++i)
+            if (i < A.nseg && tile >= A.seg[i].tile_begin)
+                s = i;
+    }
+    const MfmaSeg &S = A.seg[s];
+    const int t_in_seg = tile - S.tile_begin;
+    const int co_tile = t_in_seg % A.co_tiles;
+    const int px_tile = t_in_seg / A.co_tiles;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wc = wave % WC, wp = wave / WC;
+    const int r = lane & 15, g = lane >> 4;
+    const int KS = A.ksteps, kpt = CB == 2 ? 1 : A.cin / 128;   // K steps, per tap
+    const int nblk = MULTI ? A.cin / (32 * CB) : 1;
+    const int row_bytes = A.cin * XB / 32;
+
+    // ---- weights of this wave's 64-channel group (as in the kernel above)
+    const int ct = co_tile * WC + wc;
+    const buf_rsrc wr = make_rsrc(S.wt + (long long)ct * KS * (4 * WB), ct < A.cout_pad / 64 ? KS * (4 * WB) : 0);
+    struct Wt {
+        v4i x;
+        uint2 y;
+    };
+    auto load_w = [&](int k, int i) -> Wt {
+        Wt w;
+        const int ko = k * (4 * WB) + i * WB;
+        w.x = load_b128(wr, lane * 16, ko);
+        w.y = make_uint2(0, 0);
+        if constexpr (F6)
+            w.y = load_b64(wr, lane * 8, ko + 1024);
+        return w;
+    };
+    // the K step of tap (ty, tx), step q of block blk, in the stored order (tap,
+    // then channel)
+    auto kidx = [&](int blk, int ty, int tx, int q) -> int { return (3 * ty + tx) * kpt + blk * Q + q; };
+
+    // ---- the virtual pixels of the three runs
+    const int vw = S.w + 1, vh = S.h + 1;
+    for (int p = tid; p < NPX; p += 256) {
+        const int t = p / RUN, i = p - t * RUN;
+        const int v = px_tile * BPX - 1 + i + (t - 1) * vw;
+        int at = -1;
+        if (v >= 0) {
+            const unsigned vy = (unsigned)v / (unsigned)vw, x = (unsigned)v - vy * (unsigned)vw;
+            const unsigned n = vy / (unsigned)vh, y = vy - n * (unsigned)vh;
+            if (x < (unsigned)S.w && y < (unsigned)S.h && n < (unsigned)S.n)
+                at = (int)((n * (unsigned)S.h + y) * (unsigned)S.w + x);
         }
+        tab[p] = at;
     }
-    __syncthreads();   // every wave is done with the ring
-    // the tables of the tile's channels, and of side-0 skips RSM(k, c, d) per code
-    int32_t *prm = (int32_t *)lds;                   // [EPI_FIELDS][WC * 64]
-    int32_t *lut = prm + EPI_FIELDS * WC * 64;       // [WC * 64][QMAX + 1]
-    const bool use_lut = SKK == 1 && S.side0;
-    for (int u = tid; u < EPI_FIELDS * WC * 64; u += 256) {
-        const int f = u / (WC * 64), c = u % (WC * 64);
-        prm[u] = co_tile * (WC * 64) + c < A.cout_pad ? S.epi[f * A.cout_pad + co_tile * (WC * 64) + c] : 0;
-    }
-    if (use_lut)
-        for (int u = tid; u < WC * 64 * (QMAX + 1); u += 256)
-            lut[u] = co_tile * (WC * 64) + u / (QMAX + 1) < A.cout
-                         ? S.lut[(long long)co_tile * (WC * 64) * (QMAX + 1) + u] : 0;
     __syncthreads();
-    uint32_t outw[NJ][OW];
+
+    const buf_rsrc xr = make_rsrc(S.x, S.n * S.h * S.w * row_bytes);
+    const int cc = tid % CB, cp0 = tid / CB;
+    using piece_t = typename std::conditional<F6, v4i, uint2>::type;
+    // LDS column c of the row of virtual pixel i of a run (16-byte columns, then the
+    // 8-byte ones): XOR with i, so that 16 consecutive pixels at one column fall on
+    // all banks
+    auto xcol = [](int i, int c) -> int {
+        return CB == 8 ? c ^ (i & 7) : CB == 4 ? c ^ ((i >> 1) & 3) : c ^ ((i >> 2) & 1);
+    };
+    auto ycol = [](int i, int c) -> int {
+        return CB == 8 ? c ^ ((i >> 1) & 7) : CB == 4 ? c ^ ((i >> 2) & 3) : c ^ ((i >> 3) & 1);
+    };
+    // copy passes it0 .. it0 + n of a block: loads, then widening and LDS writes
+    auto stage = [&](int blk, int cp, auto it0c, auto nc) {
+        constexpr int it0 = decltype(it0c)::value, n = decltype(nc)::value;
+        piece_t v[n];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int o = 0; o < OW; ++o)
-            outw[j][o] = 0;
-    const int cl = 64 * wc + 16 * g;
-    const int32_t *lut_l = lut + cl * (QMAX + 1);
-    auto group = [&](auto lut_c, auto ic) {
-        constexpr bool LUT = decltype(lut_c)::value;
-        constexpr int i = decltype(ic)::value;
-        const int32_t *tab = prm + cl + 4 * i;
-        const v4i bias = *(const v4i *)(tab + EPI_BIAS * WC * 64);
-        const v4i mult = *(const v4i *)(tab + EPI_MULT * WC * 64);
-        const v4i shf = *(const v4i *)(tab + (FAST ? EPI_SHR : EPI_SHIFT) * WC * 64);
-        v4i rnd = {0, 0, 0, 0}, sc = rnd, sd = rnd, ss = rnd;
-        if constexpr (FAST)
-            rnd = *(const v4i *)(tab + EPI_RND * WC * 64);
-        long long srnd[4] = {0, 0, 0, 0};
-        if constexpr (SKK != 0 && !LUT) {
-            sc = *(const v4i *)(tab + EPI_SKIP_C * WC * 64);
-            sd = *(const v4i *)(tab + EPI_SKIP_D * WC * 64);
-            ss = *(const v4i *)(tab + EPI_SKIP_SIDE * WC * 64);
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                srnd[e] = rsm_rnd(sd[e]);
+        for (int k = 0; k < n; ++k) {
+            const int p = (it0 + k) * PPI + cp;
+            const int at = p < NPX ? tab[p] : -1;
+            const int off = at >= 0 ? at * row_bytes + blk * (XB * CB) + XB * cc : (int)0x80000000;
+            if constexpr (F6)
+                v[k] = load_b128(xr, off, 0);
+            else
+                v[k] = load_b64(xr, off, 0);
         }
 #pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int v = (int)(acc[i][j][e] * UNIT) + bias[e];
-                const int bit = (4 * i + e) * BO;
-                int kv = 0;
-                if constexpr (SKK == 1)
-                    kv = (int)__builtin_amdgcn_ubfe(skw[j][bit >> 5], bit & 31, BO);
-                int y;
-                if constexpr (FAST) {
-                    int u = v;
-                    if constexpr (LUT) {
-                        u = (int)((unsigned)v + (unsigned)lut_l[(4 * i + e) * (QMAX + 1) + kv]);
-                    } else if constexpr (SKK != 0) {
-                        const int scaled = rsm32r(ss[e] ? v : kv, sc[e], srnd[e], sd[e]);
-                        u = (int)((unsigned)scaled + (unsigned)(ss[e] ? kv : v));
-                    }
-                    y = requant32(u, mult[e], (long long)rnd[e] << 32, shf[e]);
-                    y = y < 0 ? 0 : (y > QMAX ? QMAX : y);
-                } else {
-                    long long u = v;
-                    if constexpr (LUT)
-                        u = (int)((unsigned)v + (unsigned)lut_l[(4 * i + e) * (QMAX + 1) + kv]);
-                    else if constexpr (SKK != 0)
-                        u = align_add(v, kv, sc[e], sd[e], ss[e]);
-                    y = (int)requant_clamp(u, mult[e], shf[e], QMAX);
-                    asm volatile("" : "+v"(y));   // one 64-bit product alive at a time
-                }
-                outw[j][bit >> 5] |= (uint32_t)y << (bit & 31);
+        for (int k = 0; k < n; ++k) {
+            const int p = (it0 + k) * PPI + cp;
+            if (it0 + k == IT - 1 && p >= NPX)
+                continue;
+            const int i = p - (p >= RUN ? RUN : 0) - (p >= 2 * RUN ? RUN : 0);
+            uint8_t *x = data + p * XROW + 16 * xcol(i, cc);
+            if constexpr (F6) {
+                const v8i o = spread_e2m3(v[k]);
+                *(v4i *)x = v4i{o[0], o[1], o[2], o[3]};
+                *(uint2 *)(data + NPX * XROW + p * YROW + 8 * ycol(i, cc)) = make_uint2((uint32_t)o[4], (uint32_t)o[5]);
+            } else {
+                const v8i o = spread_e2m1(v[k]);
+                *(v4i *)x = v4i{o[0], o[1], o[2], o[3]};
             }
         }
     };
-    if (use_lut)
-        static_for<MI>([&](auto ic) { group(std::true_type{}, ic); });
-    else
-        static_for<MI>([&](auto ic) { group(std::false_type{}, ic); });
-    if (F6 && A.qmax == 7) {   // 3-bit codes (clamped to 15 above)
+    // the first block: every load in flight at once (nothing else holds registers)
+    stage(0, cp0, std::integral_constant<int, 0>{}, std::integral_constant<int, IT>{});
+    Wt fa[2][MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+        fa[0][i] = load_w(0, i);
+    __syncthreads();
+
+    // ---- fragments: column tile j of tap (ty, tx), step q: virtual pixel
+    // 16 (NJ wp + j) + r + tx of run ty, chunk 4q + g
+    struct Frag {
+        v4i x;
+        uint2 y;
+    };
+    // (CB 2: a step holds two taps, lane groups 0-1 the first and 2-3 the second;
+    // ax[k], ay[k] are those of step k of the five, the last tap of the last step is
+    // past the window and meets zero weights)
+    constexpr int NA = CB == 2 ? 5 : 3;
+    uint32_t ax[NA], ay[NA];
+#pragma unroll
+    for (int k = 0; k < NA; ++k) {
+        const int tap = CB == 2 ? min(2 * k + (g >> 1), 8) : k;   // CB > 2: tap k of row 0
+        const int c = CB == 2 ? g & 1 : g;
+        const int run = tap / 3, i = 16 * NJ * wp + r + tap - 3 * run;
+        ax[k] = (uint32_t)(XROW * (run * RUN + i) + 16 * xcol(i, c));
+        ay[k] = (uint32_t)(NPX * XROW + YROW * (run * RUN + i) + 8 * ycol(i, c));
+    }
+    // (ax and ay move to window row ty0 with the loop below; rows: from there)
+    auto read_frag = [&](int rows, int tx, int q, int j) -> Frag {
+        Frag f;
+        // chunk 4 + g: bit 2 of the column flips
+        f.x = *(const v4i *)(data + (q ? ax[tx] ^ 64u : ax[tx]) + (rows * RUN + 16 * j) * XROW);
+        f.y = make_uint2(0, 0);
+        if constexpr (F6)
+            f.y = *(const uint2 *)(data + (q ? ay[tx] ^ 32u : ay[tx]) + (rows * RUN + 16 * j) * YROW);
+        return f;
+    };
+
+    v4f acc[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
-#pragma unroll
-            for (int o = 0; o < OW; ++o)
-                outw[j][o] = sat7_nibbles(outw[j][o]);
-    }
-    // the packed words are complete here (see the fences of the other kernels)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int o = 0; o < OW; ++o)
-            asm volatile("" : "+v"(outw[j][o]));
-    // a whole channel tile's codes go through LDS and out as 16-byte chunks of
-    // contiguous pixel rows; a partial one is stored from registers
-    constexpr int ROWB = WC * 64 * BO / 8, CPR = ROWB / 16;
-    if (A.cout - co_tile * (WC * 64) >= WC * 64) {
-        __syncthreads();
-        const int cb = cl * BO / 8;
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) {
-            const int p = pw + 16 * j;
-            uint8_t *d = lds + p * ROWB + 16 * ((cb >> 4) ^ (p & (CPR - 1))) + (cb & 15);
-            store_words<OW>(d, outw[j]);
+            acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    Frag fb[NJ];
+    for (int blk = 0; blk < nblk; ++blk) {
+        if (MULTI && blk) {
+            __syncthreads();   // every wave is done with the last block
+            int cp = cp0;
+            asm volatile("" : "+v"(cp));   // (addresses worked out here, not kept through the K loop)
+            static_for<(IT + 3) / 4>([&](auto bc) {
+                constexpr int it0 = 4 * decltype(bc)::value;
+                stage(blk, cp, std::integral_constant<int, it0>{}, std::integral_constant<int, (IT - it0 < 4 ? IT - it0 : 4)>{});
+            });
+            __syncthreads();
         }
-        __syncthreads();
-        const long long rowg = (long long)A.cout * BO / 8;
 #pragma unroll
-        for (int it = 0; it < (BPX * CPR + 255) / 256; ++it) {
-            const int idx = it * 256 + tid;
-            const int p = idx / CPR, c = idx % CPR;
-            const long long px = (long long)px_tile * BPX + p;
-            if (p < BPX && px < S.P)
-                *(uint4 *)((uint8_t *)S.y + px * rowg + co_tile * ROWB + 16 * c) =
-                    *(const uint4 *)(lds + p * ROWB + 16 * (c ^ (p & (CPR - 1))));
+        for (int j = 0; j < RA; ++j)
+            fb[j] = read_frag(0, 0, 0, j);
+        // window rows; with one K step per tap (odd counts per row) all nine taps
+        // are one body, so that the weight sets stay compile-time
+        constexpr int TYU = Q == 1 ? 3 : 1, U = CB == 2 ? 5 : 3 * Q * TYU;
+        for (int ty0 = 0; ty0 < 3; ty0 += TYU) {
+            static_for<U>([&](auto uc) {
+                constexpr int u = decltype(uc)::value;
+                constexpr int un = u + 1 < U ? u + 1 : 0;
+                constexpr int tx = CB == 2 ? u : u / Q % 3, q = u % Q;
+                constexpr int txn = CB == 2 ? un : un / Q % 3, qn = un % Q;
+                constexpr int row = CB == 2 ? 0 : u / (3 * Q);
+                // the next step; after the block's last: the next block's first
+                // (after the last block's: read, not used)
+                const int rown = CB == 2 ? 0 : u + 1 < U ? (u + 1) / (3 * Q) : ty0 + TYU < 3 ? TYU : -ty0;
+                const int bn = u + 1 < U || ty0 + TYU < 3 ? blk : blk + 1;
+                const int kn = bn < nblk ? kidx(bn, CB == 2 ? 0 : ty0 + rown, txn, qn) : 0;
+                static_for<NJ>([&](auto jc) {
+                    constexpr int j = decltype(jc)::value;
+                    if constexpr (j < 2) {
+                        fa[(u + 1) % 2][2 * j] = load_w(kn, 2 * j);
+                        fa[(u + 1) % 2][2 * j + 1] = load_w(kn, 2 * j + 1);
+                    }
+                    if constexpr (j + RA < NJ)
+                        fb[j + RA] = read_frag(row, tx, q, j + RA);
+                    else
+                        fb[j + RA - NJ] = read_frag(rown, txn, qn, j + RA - NJ);
+                    const v8i b = v8i{fb[j].x.x, fb[j].x.y, fb[j].x.z, fb[j].x.w, (int)fb[j].y.x, (int)fb[j].y.y, 0, 0};
+#pragma unroll
+                    for (int i = 0; i < MI; ++i) {
+                        const Wt &w = fa[u % 2][i];
+                        acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
+                            v8i{w.x.x, w.x.y, w.x.z, w.x.w, (int)w.y.x, (int)w.y.y, 0, 0}, b, acc[i][j],
+                            F6 ? 2 : 4, F6 ? 2 : 4, 0, 0, 0, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            });
+            const int d = ty0 + TYU < 3 ? TYU : -ty0;
+#pragma unroll
+            for (int tx = 0; tx < (CB == 2 ? 0 : 3); ++tx) {
+                ax[tx] += (uint32_t)(d * (RUN * XROW));
+                ay[tx] += (uint32_t)(d * (RUN * YROW));
+            }
         }
-        return;
     }
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-        if (co_ok && pxw + 16 * j < S.P)
-            store_words<OW>((uint8_t *)S.y + ((pxw + 16 * j) * A.cout + c0) * BO / 8, outw[j]);
+    // (the thread's number from its lane, so that none is held through the K loop)
+    const int tid2 = 64 * wave + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    fx_epilogue<KIND, WC, NJ, OUTK, SKK, FAST>(A, S, data, acc, co_tile, tid2, [&](int p) -> long long {
+        return tab[RUN + 1 + p];
+    });
 }
 
 template <int KIND, int WC, int NJ>
@@ -498,9 +782,43 @@ hipError_t launch_modes(const MfmaArgs &a, bool fast, hipStream_t stream)
     return hipGetLastError();
 }
 
+template <int KIND, int WC, int NJ, int CB, int MULTI>
+hipError_t launch3_modes(const MfmaArgs &a, bool fast, hipStream_t stream)
+{
+    const dim3 grid(8 * a.tiles_per_xcd), block(256);
+    if (a.bits_out == 32)
+        hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 1, 0, 1, CB, MULTI>), grid, block, 0, stream, a);
+    else if (a.skip_bits == 0 && fast)
+        hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 0, 0, 1, CB, MULTI>), grid, block, 0, stream, a);
+    else if (a.skip_bits == 0)
+        hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 0, 0, 0, CB, MULTI>), grid, block, 0, stream, a);
+    else if constexpr (NJ == 8)
+        return hipErrorInvalidValue;   // (as above: no room for the skip codes)
+    else if (fast)
+        hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 0, 1, 1, CB, MULTI>), grid, block, 0, stream, a);
+    else
+        hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 0, 1, 0, CB, MULTI>), grid, block, 0, stream, a);
+    return hipGetLastError();
+}
+
 template <int KIND>
 hipError_t launch_kind(const MfmaArgs &a, const GfPlan &p, bool fast, hipStream_t stream)
 {
+    if (p.kw < 0) {   // 3x3, stride 1: the input tile in LDS
+        const int tile = p.mi * 10 + p.nj;
+        if (a.cin == 256)
+            return tile == 48   ? launch3_modes<KIND, 4, 8, 8, 0>(a, fast, stream)
+                   : tile == 44 ? launch3_modes<KIND, 4, 4, 8, 0>(a, fast, stream)
+                   : tile == 24 ? launch3_modes<KIND, 2, 4, 8, 0>(a, fast, stream)
+                                : hipErrorInvalidValue;
+        if (a.cin == 128)
+            return tile == 48   ? launch3_modes<KIND, 4, 8, 4, 0>(a, fast, stream)
+                   : tile == 24 ? launch3_modes<KIND, 2, 4, 4, 0>(a, fast, stream)
+                                : hipErrorInvalidValue;
+        if (a.cin == 64)
+            return tile == 14 ? launch3_modes<KIND, 1, 4, 2, 0>(a, fast, stream) : hipErrorInvalidValue;
+        return tile == 44 ? launch3_modes<KIND, 4, 4, 8, 1>(a, fast, stream) : hipErrorInvalidValue;
+    }
     switch (p.mi * 10 + p.nj) {   // waves along channels, column tiles per wave
     case 48: return launch_modes<KIND, 4, 8>(a, fast, stream);
     case 44: return launch_modes<KIND, 4, 4>(a, fast, stream);
@@ -522,9 +840,12 @@ hipError_t launch_qconv_fx(const MfmaArgs &a, const GfPlan &p, hipStream_t strea
                                 (a.skip_bits != 0 && a.skip_bits != a.bits_out)) ||
         (long long)a.ksteps * 4 * (f6 ? GF_F6_TILE : 1024) >= (1LL << 31))
         return hipErrorInvalidValue;
-    // 32-bit buffer offsets and pixel numbers
+    if (p.kw < 0 && (a.kh != 3 || a.kw != 3 || a.stride != 1 || a.pad != 1 || (a.cin % 256 != 0 && a.cin != 128 && a.cin != 64)))
+        return hipErrorInvalidValue;
+    // 32-bit buffer offsets and pixel numbers (virtual pixels: at most 4 per pixel)
     for (int i = 0; i < a.nseg; ++i)
-        if ((long long)a.seg[i].n * a.seg[i].h * a.seg[i].w * a.cin / (f6 ? 2 : 4) >= (1LL << 31) ||
+        if ((p.kw < 0 && (long long)a.seg[i].n * (a.seg[i].h + 1) * (a.seg[i].w + 1) + 512 >= (1LL << 31)) ||
+            (long long)a.seg[i].n * a.seg[i].h * a.seg[i].w * a.cin / (f6 ? 2 : 4) >= (1LL << 31) ||
             a.seg[i].P + 256 >= (1LL << 31))
             return hipErrorInvalidValue;
     bool fast = true;

@@ -55,11 +55,11 @@ CASES = {
 # (more than one group past the last), ragged pixel tiles, skips of mixed and
 # zero sides, the 64-bit requantisation (shifts below 2)
 TILED = {
-    "f6_256x128": dict(n=2, h=97, w=91, cin=256, cout=256, k=3, wenc=1),
-    "f6_256x128_partial_cout": dict(n=1, h=97, w=91, cin=128, cout=592, k=3, wenc=1),
+    "f6_256x128": dict(n=2, h=193, w=181, cin=256, cout=256, k=3, stride=2, wenc=1),
+    "f6_256x128_partial_cout": dict(n=1, h=97, w=91, cin=160, cout=592, k=3, wenc=1),
     "f6_256x128_int32": dict(n=1, h=75, w=91, cin=160, cout=720, k=3, bits_out=32, wenc=1),
     "f6_256x64": dict(n=1, h=67, w=75, cin=1024, cout=512, k=1),
-    "f6_256x64_skip_cin96": dict(n=1, h=83, w=75, cin=160, cout=512, k=3, skip_bits=4),
+    "f6_256x64_skip_cin160": dict(n=1, h=83, w=75, cin=160, cout=512, k=3, skip_bits=4),
     "f6_256x64_3bit": dict(n=1, h=83, w=75, cin=192, cout=384, k=3, bits_in=3, bits_w=3, bits_out=3, wenc=1),
     "f6_128x128_int32": dict(n=2, h=131, w=141, cin=160, cout=80, k=3, bits_out=32, wenc=1),
     "f6_128x128_stride2": dict(n=2, h=261, w=251, cin=128, cout=128, k=3, stride=2, wenc=1),
@@ -68,6 +68,28 @@ TILED = {
                                skip_up2=True),
     "f4_256x128_int32": dict(n=1, h=201, w=203, cin=96, cout=516, k=3, bits_in=2, bits_w=2, bits_out=32, wenc=1),
     "f4_128x128": dict(n=2, h=131, w=141, cin=96, cout=112, k=3, bits_in=2, bits_w=2, bits_out=2, skip_bits=2),
+    # 3x3 stride 1 with the tile's input in LDS: every block size (64, 128, 256
+    # channels, two blocks), tiles that span rows, images and pads (rows shorter
+    # than a tile, 1-pixel images), partial channel tiles
+    "fx3_cin64": dict(n=3, h=61, w=77, cin=64, cout=64, k=3, wenc=1),
+    "fx3_cin64_skip_3bit": dict(n=3, h=61, w=77, cin=64, cout=80, k=3, bits_in=3, bits_w=3, bits_out=3, skip_bits=3),
+    "fx3_cin64_int32": dict(n=40, h=23, w=15, cin=64, cout=36, k=3, bits_out=32, wenc=1),
+    "fx3_cin128": dict(n=17, h=23, w=19, cin=128, cout=128, k=3, wenc=1),
+    "fx3_cin128_skip": dict(n=17, h=23, w=19, cin=128, cout=112, k=3, wenc=1, skip_bits=4),
+    "fx3_cin256_256x64": dict(n=3, h=31, w=41, cin=256, cout=256, k=3, wenc=1),
+    "fx3_cin256_256x128": dict(n=9, h=41, w=47, cin=256, cout=272, k=3, wenc=1),
+    "fx3_cin256_128x128_skip": dict(n=9, h=21, w=47, cin=256, cout=256, k=3, wenc=1, skip_bits=4),
+    "fx3_cin256_256x64_skip": dict(n=9, h=51, w=57, cin=256, cout=256, k=3, wenc=1, skip_bits=4),
+    "fx3_cin256_int32": dict(n=5, h=41, w=47, cin=256, cout=324, k=3, bits_out=32, wenc=1),
+    "fx3_cin256_narrow_int32": dict(n=9, h=41, w=47, cin=256, cout=80, k=3, bits_out=32, wenc=1),
+    "fx3_cin512_skip": dict(n=3, h=25, w=27, cin=512, cout=528, k=3, skip_bits=4),
+    "fx3_1x1_images": dict(n=3500, h=1, w=1, cin=256, cout=256, k=3, wenc=1),
+    "fx3_2x300": dict(n=7, h=2, w=300, cin=128, cout=256, k=3, wenc=1),
+    "fx3_f4_cin64": dict(n=3, h=61, w=77, cin=64, cout=64, k=3, bits_in=2, bits_w=2, bits_out=2, wenc=1, skip_bits=2),
+    "fx3_f4_cin128": dict(n=17, h=23, w=19, cin=128, cout=128, k=3, bits_in=2, bits_w=2, bits_out=2),
+    "fx3_f4_cin256": dict(n=3, h=61, w=77, cin=256, cout=272, k=3, bits_in=2, bits_w=2, bits_out=2, skip_bits=2),
+    "fx3_f4_cin256_int32": dict(n=2, h=91, w=97, cin=256, cout=720, k=3, bits_in=2, bits_w=2, bits_out=32, wenc=1),
+    "fx3_f4_cin512": dict(n=3, h=25, w=27, cin=512, cout=512, k=3, bits_in=2, bits_w=2, bits_out=2, wenc=1),
 }
 
 
@@ -80,11 +102,11 @@ def test_tiled_parity(torch, name):
 def test_tiled_epilogue_forms(torch, bits, skip):
     """64-bit requantisation (a shift below 2), and skips whose sides are all 0
     (the table of scaled codes)."""
-    for form in ("slow", "side0"):
-        case = workloads.random_conv_case(seed=61 + bits, n=1, h=83, w=75, cin=512, cout=512, k=3, bits_in=bits,
-                                          bits_w=bits, bits_out=bits, skip_bits=skip)
+    for form in ("slow", "side0", "slow 3x3", "side0 3x3"):
+        case = workloads.random_conv_case(seed=61 + bits, n=1, h=83, w=75, cin=256 if "3x3" in form else 160, cout=512,
+                                          k=3, bits_in=bits, bits_w=bits, bits_out=bits, skip_bits=skip)
         lv = case.levels[0]
-        if form == "slow":
+        if "slow" in form:
             lv["shift"][5] = 1
             lv["mult"][5] = 1 << 30
         elif skip:
