@@ -170,6 +170,56 @@ std::vector<uint8_t> gf_weights(int kind, int cout, int taps, int cin, int group
     return out;
 }
 
+// Requantisation in fp32 (Eq. 2 on integers, reading R2: code m and above from the
+// accumulator T_m = ceil((2m - 1) 2^(d-1) / M) on, d = 31 + shift). floor(v a + b) in
+// one fused multiply-add gives the same code for every integer v that fp32 holds
+// (|v| <= 2^24) if
+//     T_m a + b >= m   and   (T_m - 1) a + b <= m - ulp    for m = 1 .. qmax,
+// since the rounded value is monotone in the exact one, m and the next smaller float
+// are floats, and both sides are monotone in v. a = M / 2^d rounded to fp32, or a
+// neighbour of it; *lo .. *hi is the interval that remains for b (usually a large
+// part of a, always some of it but for the rounding of a). False if none does: the
+// level then keeps the integer form.
+bool float_requant(int mult, int shift, int qmax, float *a, double *lo, double *hi)
+{
+    if (mult <= 0 || shift < 2 || shift > 28)
+        return false;
+    const int d = 31 + shift;
+    const float a0 = (float)std::ldexp((double)mult, -d);
+    double t[16], width = -1.0;
+    for (int m = 1; m <= qmax; ++m) {
+        const uint64_t num = (uint64_t)(2 * m - 1) << (d - 1);   // < 2^5 * 2^58
+        t[m] = (double)((num + (uint64_t)mult - 1) / (uint64_t)mult);
+    }
+    for (int step = 0; step <= 4 && width < 8e-6; ++step)
+        for (int sign = -1; sign <= 1; sign += 2) {
+            float c = a0;
+            for (int k = 0; k < step; ++k)
+                c = std::nextafterf(c, sign > 0 ? 2 * a0 : 0.f);
+            double l = -1e30, u = 1e30;
+            for (int m = 1; m <= qmax; ++m) {
+                l = std::fmax(l, m - t[m] * c);
+                u = std::fmin(u, m - std::ldexp((double)m, -23) - (t[m] - 1) * c);
+            }
+            if (u - l > width) {
+                width = u - l;
+                *a = c;
+                *lo = l + 1e-9;   // (the doubles above are within 1e-13)
+                *hi = u - 1e-9;
+            }
+        }
+    return width > 2e-9;
+}
+
+// b for accumulators that lack `missing`: v = acc + missing
+bool float_offset(float a, double lo, double hi, double missing, int32_t *bits)
+{
+    const double at = missing * a;
+    const float b = (float)(at + (lo + hi) / 2);
+    std::memcpy(bits, &b, 4);
+    return b - at >= lo && b - at <= hi;
+}
+
 int pick_tile(int cout, bool codes, int bits_in)
 {
     if (bits_in == 4 && cout >= 256 && (!codes || cout % 32 == 0))
@@ -219,7 +269,10 @@ struct qconv_s {
     void *w_dev;       // the one allocation: weights, then the parts below
     int32_t *epi_dev;  // [num_levels][EPI_FIELDS][cout_pad]
     int32_t *lut_dev;  // code skips: [num_levels][cout_pad][2^skip_bits] RSM(k, c, d), else null
-    std::vector<int> fast;  // per level: every shift >= 2
+    int32_t *lutf_dev, *gf_lutf;  // the same shape: fp32 b per code
+    // per level: 1 = every shift >= 2, 2 = fp32 requantisation too; gf_fast: for the
+    // block-float kernels, whose accumulators enter it without the bias
+    std::vector<int> fast, gf_fast;
     std::vector<int> side0; // per level: every skip side is 0
     const uint8_t *zero;    // the device's zero page
     // global-fed kernel: operand kind (GF_NONE: not available), 64-channel
@@ -359,6 +412,7 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     h.cout_pad = mfma ? h.co_tiles * BLK_CO : d.cout;
     h.ksteps = stem ? 3 : mfma ? taps * (d.cin / KC) : 0;
     h.fast.assign(d.num_levels, 0);
+    h.gf_fast.assign(d.num_levels, 0);
     h.side0.assign(d.num_levels, 0);
     for (int l = 0; l < d.num_levels && d.skip_bits; ++l) {  // (stored widths from here on)
         int ok = 1;
@@ -461,8 +515,6 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
                 const int sh = e.shift[c];
                 t[EPI_MULT * h.cout_pad + c] = e.mult[c];
                 t[EPI_SHIFT * h.cout_pad + c] = sh;
-                t[EPI_SHR * h.cout_pad + c] = sh - 1;
-                t[EPI_RND * h.cout_pad + c] = sh >= 2 ? (1 << (sh - 2)) : 0;
             }
             if (d.skip_bits) {
                 t[EPI_SKIP_C * h.cout_pad + c] = e.skip_c[c];
@@ -531,6 +583,57 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
                 }
     }
 
+    // fp32 requantisation, where it is exact: codes of at most 4 bits, no skip or code
+    // skips of side 0 (an offset per code). a and b per channel, for v = acc + bias
+    // (tables and lutf) and for the block-float accumulators (gf tables and glutf)
+    std::vector<int32_t> lutf(lut.size()), glutf(lut.size());
+    const int qmax = codes ? (1 << dc.bits_out) - 1 : 0;
+    for (int l = 0; l < d.num_levels && codes && dc.bits_out <= 4 && d.skip_bits <= 4; ++l) {
+        if (!h.fast[l] || (d.skip_bits && !h.side0[l]))
+            continue;
+        const qconv_epilogue_t &e = levels[l];
+        int32_t *t = epi.data() + (size_t)l * EPI_FIELDS * h.cout_pad;
+        const int gpad = 64 * h.gf_groups;
+        int32_t *gt = gfe.data() + (size_t)l * EPI_FIELDS * gpad;
+        const float unit = h.gf_kind == GF_F6 ? 64.f : h.gf_kind == GF_F4 ? 2.f : 1.f;
+        bool ok = true, gok = h.gf_kind != GF_NONE;
+        for (int c = 0; c < d.cout && (ok || gok); ++c) {
+            float a = 0.f;
+            double lo = 0, hi = 0;
+            if (!float_requant(e.mult[c], e.shift[c], qmax, &a, &lo, &hi)) {
+                ok = gok = false;
+                break;
+            }
+            // (the tables' bias: re-centred for 8-bit codes)
+            const double bias = t[EPI_BIAS * h.cout_pad + c];
+            ok = ok && K * ((1 << dc.bits_in) - 1) * wmax + std::fabs(bias) < (1 << 24);
+            std::memcpy(&t[EPI_FA * h.cout_pad + c], &a, 4);
+            ok = ok && float_offset(a, lo, hi, 0, &t[EPI_FB * h.cout_pad + c]);
+            if (gok) {
+                const double gbias = gt[EPI_BIAS * gpad + c];
+                const float ga = a * unit;
+                std::memcpy(&gt[EPI_FA * gpad + c], &ga, 4);
+                gok = h.gf_kind != GF_I8 || K * ((1 << dc.bits_in) - 1) * wmax < (1 << 24);
+                gok = gok && float_offset(a, lo, hi, gbias, &gt[EPI_FB * gpad + c]);
+            }
+            for (int k = 0; k < nk; ++k) {
+                const size_t at = ((size_t)l * h.cout_pad + c) * nk + k;
+                const long long p = (long long)k * e.skip_c[c];
+                const int dd = e.skip_d[c];
+                const double r = (double)(dd > 0 ? (p + (1LL << (dd - 1))) >> dd : p);
+                ok = ok && float_offset(a, lo, hi, r, &lutf[at]);
+                gok = gok && float_offset(a, lo, hi, r + gt[EPI_BIAS * gpad + c], &glutf[at]);
+            }
+        }
+        if (ok)
+            h.fast[l] = 2;
+        if (gok)
+            h.gf_fast[l] = 2;
+    }
+    for (int l = 0; l < d.num_levels; ++l)
+        if (!h.gf_fast[l])
+            h.gf_fast[l] = h.fast[l] ? 1 : 0;
+
     const char *inject = std::getenv("AQD_FAULT_INJECT");
     if (inject && std::strcmp(inject, "alloc") == 0)
         return fail(AQD_ERR_NOMEM, "device allocation failed (injected)");
@@ -547,7 +650,8 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     // look-ahead may read (never use)
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t o_epi = up(wbuf.size() + (mfma ? 4 * 256 * KC : 0)), o_lut = o_epi + up(epi.size() * sizeof(int32_t)),
-                 o_gfw = o_lut + up(lut.size() * sizeof(int32_t)), o_gfe = o_gfw + up(gfw.size()),
+                 o_lutf = o_lut + up(lut.size() * sizeof(int32_t)), o_glutf = o_lutf + up(lut.size() * sizeof(int32_t)),
+                 o_gfw = o_glutf + up(lut.size() * sizeof(int32_t)), o_gfe = o_gfw + up(gfw.size()),
                  total = o_gfe + gfe.size() * sizeof(int32_t);
     if (hipMalloc(&hp->w_dev, total) != hipSuccess) {
         delete hp;
@@ -558,9 +662,11 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
         const void *src;
         size_t n;
     };
-    const Part parts[5] = {{0, wbuf.data(), wbuf.size()},
+    const Part parts[7] = {{0, wbuf.data(), wbuf.size()},
                            {o_epi, epi.data(), epi.size() * sizeof(int32_t)},
                            {o_lut, lut.data(), lut.size() * sizeof(int32_t)},
+                           {o_lutf, lutf.data(), lutf.size() * sizeof(int32_t)},
+                           {o_glutf, glutf.data(), glutf.size() * sizeof(int32_t)},
                            {o_gfw, gfw.data(), gfw.size()},
                            {o_gfe, gfe.data(), gfe.size() * sizeof(int32_t)}};
     bool copied = true;
@@ -583,6 +689,8 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     uint8_t *base = (uint8_t *)hp->w_dev;
     hp->epi_dev = (int32_t *)(base + o_epi);
     hp->lut_dev = nk ? (int32_t *)(base + o_lut) : nullptr;
+    hp->lutf_dev = nk ? (int32_t *)(base + o_lutf) : nullptr;
+    hp->gf_lutf = nk ? (int32_t *)(base + o_glutf) : nullptr;
     hp->gf_w = base + o_gfw;
     hp->gf_epi = (int32_t *)(base + o_gfe);
     *out = hp;
@@ -883,6 +991,20 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
         REQUIRE(tiles + px_tiles * co_tiles < (1LL << 26), "too many tiles for one launch");
         tiles += (int)(px_tiles * co_tiles);
     }
+    // fp32 requantisation when every segment has it (4-bit codes in and out)
+    bool f32 = h0.d.bits_in == 4 && h0.d.out_mode == AQD_OUT_CODES && h0.d.bits_out == 4 && h0.d.skip_bits <= 4;
+    for (int i = 0; i < a.nseg; ++i)
+        f32 = f32 && a.seg[i].fast == 2;
+    const size_t lut_words = (size_t)h0.cout_pad * (1 << (h0.d.skip_bits & 15));
+    for (int i = 0, k = 0; i < count; ++i) {
+        if (segs[i].n == 0)
+            continue;
+        MfmaSeg &m = a.seg[k++];
+        if (!f32)
+            m.fast = m.fast ? 1 : 0;
+        else if (h0.d.skip_bits)
+            m.lut = segs[i].conv->lutf_dev + segs[i].level * lut_words;
+    }
     a.total_tiles = tiles;
     a.tiles_per_xcd = (tiles + 7) / 8;
     a.ksplit = 1;
@@ -1017,6 +1139,9 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
     const int px = wc ? 16 * nj * (4 / wc) : 16 * plan->nj;
     MfmaArgs &a = *out;
     a = MfmaArgs{};
+    bool f32 = codes;   // fp32 requantisation when every segment has it
+    for (int i = 0; i < count; ++i)
+        f32 = f32 && (segs[i].n == 0 || segs[i].conv->gf_fast[segs[i].level] == 2);
     long long tiles = 0;
     for (int i = 0; i < count; ++i) {
         const qconv_seg_t &s = segs[i];
@@ -1037,10 +1162,10 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
         m.hs = s.hs;
         m.ws = s.ws;
         m.tile_begin = (int)tiles;
-        m.fast = s.conv->fast[s.level];
+        m.fast = f32 ? 2 : s.conv->gf_fast[s.level] ? 1 : 0;
         m.side0 = s.conv->side0[s.level];
-        m.lut = s.conv->lut_dev ? s.conv->lut_dev + (size_t)s.level * s.conv->cout_pad * (1 << h0.d.skip_bits)
-                                : nullptr;
+        if (s.conv->lut_dev)
+            m.lut = (f32 ? s.conv->gf_lutf : s.conv->lut_dev) + (size_t)s.level * s.conv->cout_pad * (1 << h0.d.skip_bits);
         const long long vp = plan->kw < 0 ? (long long)s.n * (s.h + 1) * (s.w + 1) : m.P;  // virtual pixels
         tiles += (vp + px - 1) / px * groups;
         if (tiles >= (1LL << 26))
@@ -1364,7 +1489,7 @@ aqd_status_t qconv_run_proj(qconv_t conv, qconv_t proj, int level, int n, int h,
     m.hs = ho;
     m.ws = wo;
     m.tile_begin = 0;
-    m.fast = conv->fast[level];
+    m.fast = conv->fast[level] ? 1 : 0;   // (the projection's alignment is an integer one)
     m.side0 = 0;
     m.x2 = (const uint8_t *)xp;
     m.wt2 = (const int8_t *)proj->w_dev;

@@ -56,7 +56,7 @@ void mfma_tile_shape(int tile_cfg, int *blk_co, int *blk_px, int *chan_per_lane)
 enum {
     EPI_BIAS = 0, EPI_MULT = 1, EPI_SHIFT = 2,            // v = acc + bias; requant M / 2^(31+shift)
     EPI_SKIP_C = 3, EPI_SKIP_D = 4, EPI_SKIP_SIDE = 5,    // Eq. 7-8 alignment
-    EPI_SHR = 6, EPI_RND = 7,                             // shift - 1 and 2^(shift-2) (shift >= 2)
+    EPI_FA = 6, EPI_FB = 7,                               // fp32 requantisation: code = floor(v * a + b), clamped
     EPI_FIELDS = 8
 };
 
@@ -69,9 +69,10 @@ struct MfmaSeg {
     long long P;         // n * ho * wo
     int n, h, w, ho, wo, hs, ws;
     int tile_begin;      // first workgroup tile of this segment
-    int fast;            // every shift of the level >= 2: 32-bit requantisation
+    int fast;            // 1: every shift of the level >= 2 (32-bit requantisation), 2: fp32 too
     int side0;           // every skip side of the level is 0 (code skips use a table)
-    const int32_t *lut;  // code skips: [cout_pad][2^bits] RSM(k, c, d) of the level
+    const int32_t *lut;  // code skips: [cout_pad][2^bits] RSM(k, c, d) of the level; in a launch
+                         // whose segments are all fast 2: the fp32 b of each code instead
     // projection shortcut (fused launch only): 1x1 conv of x2 whose int32 output is the skip
     const uint8_t *x2;   // [n][h2][w2][cin2] codes
     const int8_t *wt2;   // its weight tiles (same tile layout)

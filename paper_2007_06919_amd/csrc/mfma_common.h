@@ -109,6 +109,18 @@ __device__ __forceinline__ int requant32(int u, int m, long long rnd_hi, int shr
 }
 
 
+// the rounding term of requant32 for a shift >= 2
+__device__ __forceinline__ long long requant_rnd(int shift) { return (long long)(1 << (shift - 2)) << 32; }
+
+// Requantisation in fp32 (FAST 2): one fused multiply-add, a clamp and a
+// truncation, for levels whose (a, b) were checked at create to give the integer
+// result for every accumulator (float_requant in aqd_api.hip). The 64-bit
+// multiply-add of requant32 takes four issue slots, this whole step three.
+__device__ __forceinline__ int quant_f32(float x, float a, float b, float qmax)
+{
+    return (int)(unsigned)__builtin_amdgcn_fmed3f(__builtin_fmaf(x, a, b), 0.f, qmax);
+}
+
 // XOR swizzle of the 16-byte columns of weight row r (64-byte rows): the
 // 16-byte reads of 16 consecutive rows at one logical column hit distinct
 // banks whether 8 or 16 lanes are served per cycle.

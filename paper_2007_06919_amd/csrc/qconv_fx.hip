@@ -158,11 +158,9 @@ __device__ __forceinline__ void fx_epilogue(const MfmaArgs &A, const MfmaSeg &S,
         constexpr int i = decltype(ic)::value;
         const int32_t *tab = prm + cl + 4 * i;
         const v4i bias = *(const v4i *)(tab + EPI_BIAS * WC * 64);
-        const v4i mult = *(const v4i *)(tab + EPI_MULT * WC * 64);
-        const v4i shf = *(const v4i *)(tab + (FAST ? EPI_SHR : EPI_SHIFT) * WC * 64);
-        v4i rnd = {0, 0, 0, 0}, sc = rnd, sd = rnd, ss = rnd;
-        if constexpr (FAST)
-            rnd = *(const v4i *)(tab + EPI_RND * WC * 64);
+        const v4i mult = *(const v4i *)(tab + (FAST == 2 ? EPI_FB : EPI_MULT) * WC * 64);
+        const v4i shf = *(const v4i *)(tab + (FAST == 2 ? EPI_FA : EPI_SHIFT) * WC * 64);
+        v4i sc = {0, 0, 0, 0}, sd = sc, ss = sc;
         long long srnd[4] = {0, 0, 0, 0};
         if constexpr (SKK != 0 && !LUT) {
             sc = *(const v4i *)(tab + EPI_SKIP_C * WC * 64);
@@ -176,13 +174,18 @@ __device__ __forceinline__ void fx_epilogue(const MfmaArgs &A, const MfmaSeg &S,
         for (int j = 0; j < NJ; ++j) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int v = (int)(acc[i][j][e] * UNIT) + bias[e];
+                const int v = FAST == 2 ? 0 : (int)(acc[i][j][e] * UNIT) + bias[e];
                 const int bit = (4 * i + e) * BO;
                 int kv = 0;
                 if constexpr (SKK == 1)
                     kv = (int)__builtin_amdgcn_ubfe(skw[j][bit >> 5], bit & 31, BO);
                 int y;
-                if constexpr (FAST) {
+                if constexpr (FAST == 2) {   // the accumulator itself: the tables hold the bias and its unit
+                    float b = __int_as_float(mult[e]);
+                    if constexpr (LUT)
+                        b = __int_as_float(lut_l[(4 * i + e) * (QMAX + 1) + kv]);
+                    y = quant_f32(acc[i][j][e], __int_as_float(shf[e]), b, (float)QMAX);
+                } else if constexpr (FAST) {
                     int u = v;
                     if constexpr (LUT) {
                         u = (int)((unsigned)v + (unsigned)lut_l[(4 * i + e) * (QMAX + 1) + kv]);
@@ -190,7 +193,7 @@ __device__ __forceinline__ void fx_epilogue(const MfmaArgs &A, const MfmaSeg &S,
                         const int scaled = rsm32r(ss[e] ? v : kv, sc[e], srnd[e], sd[e]);
                         u = (int)((unsigned)scaled + (unsigned)(ss[e] ? kv : v));
                     }
-                    y = requant32(u, mult[e], (long long)rnd[e] << 32, shf[e]);
+                    y = requant32(u, mult[e], requant_rnd(shf[e]), shf[e] - 1);
                     y = y < 0 ? 0 : (y > QMAX ? QMAX : y);
                 } else {
                     long long u = v;
@@ -205,9 +208,9 @@ __device__ __forceinline__ void fx_epilogue(const MfmaArgs &A, const MfmaSeg &S,
             }
         }
     };
-    if (use_lut)
-        static_for<MI>([&](auto ic) { group(std::true_type{}, ic); });
-    else
+    if (FAST == 2 ? SKK == 1 : use_lut)
+        static_for<MI>([&](auto ic) { group(std::integral_constant<bool, SKK == 1>{}, ic); });
+    else if constexpr (FAST != 2 || SKK != 1)
         static_for<MI>([&](auto ic) { group(std::false_type{}, ic); });
     if (F6 && A.qmax == 7) {   // 3-bit codes (clamped to 15 above)
 #pragma unroll
@@ -257,7 +260,8 @@ __device__ __forceinline__ void fx_epilogue(const MfmaArgs &A, const MfmaSeg &S,
 
 
 // OUTK: 0 = codes of the input's width, 1 = int32; SKK: 0 = none, 1 = codes of
-// the input's width; FAST: every shift >= 2 (32-bit requantisation); OCC:
+// the input's width; FAST: 1 = every shift >= 2 (32-bit requantisation), 2 = fp32
+// requantisation (skips: all of side 0); OCC:
 // workgroups per CU
 template <int KIND, int WC, int NJ, int OUTK, int SKK, int FAST, int OCC>
 __global__ void __launch_bounds__(256, OCC) qconv_fx_kernel(MfmaArgs A)
@@ -762,19 +766,23 @@ __global__ void __launch_bounds__(256, 2) qconv_fx3_kernel(MfmaArgs A)
 }
 
 template <int KIND, int WC, int NJ>
-hipError_t launch_modes(const MfmaArgs &a, bool fast, hipStream_t stream)
+hipError_t launch_modes(const MfmaArgs &a, int fast, hipStream_t stream)
 {
     const dim3 grid(8 * a.tiles_per_xcd), block(256);
     // workgroups per CU: what the registers allow without spilling
     constexpr int OCC = NJ == 4 && KIND == GF_F4 ? 3 : 2;
     if (a.bits_out == 32)
         hipLaunchKernelGGL((qconv_fx_kernel<KIND, WC, NJ, 1, 0, 1, 2>), grid, block, 0, stream, a);
+    else if (a.skip_bits == 0 && fast == 2)
+        hipLaunchKernelGGL((qconv_fx_kernel<KIND, WC, NJ, 0, 0, 2, OCC>), grid, block, 0, stream, a);
     else if (a.skip_bits == 0 && fast)
         hipLaunchKernelGGL((qconv_fx_kernel<KIND, WC, NJ, 0, 0, 1, OCC>), grid, block, 0, stream, a);
     else if (a.skip_bits == 0)
         hipLaunchKernelGGL((qconv_fx_kernel<KIND, WC, NJ, 0, 0, 0, 2>), grid, block, 0, stream, a);
     else if constexpr (NJ == 8 && KIND == GF_F6)
         return hipErrorInvalidValue;   // the skip codes do not fit beside 128 accumulators
+    else if (fast == 2)
+        hipLaunchKernelGGL((qconv_fx_kernel<KIND, WC, NJ, 0, 1, 2, 2>), grid, block, 0, stream, a);
     else if (fast)
         hipLaunchKernelGGL((qconv_fx_kernel<KIND, WC, NJ, 0, 1, 1, 2>), grid, block, 0, stream, a);
     else
@@ -783,17 +791,21 @@ hipError_t launch_modes(const MfmaArgs &a, bool fast, hipStream_t stream)
 }
 
 template <int KIND, int WC, int NJ, int CB, int MULTI>
-hipError_t launch3_modes(const MfmaArgs &a, bool fast, hipStream_t stream)
+hipError_t launch3_modes(const MfmaArgs &a, int fast, hipStream_t stream)
 {
     const dim3 grid(8 * a.tiles_per_xcd), block(256);
     if (a.bits_out == 32)
         hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 1, 0, 1, CB, MULTI>), grid, block, 0, stream, a);
+    else if (a.skip_bits == 0 && fast == 2)
+        hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 0, 0, 2, CB, MULTI>), grid, block, 0, stream, a);
     else if (a.skip_bits == 0 && fast)
         hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 0, 0, 1, CB, MULTI>), grid, block, 0, stream, a);
     else if (a.skip_bits == 0)
         hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 0, 0, 0, CB, MULTI>), grid, block, 0, stream, a);
     else if constexpr (NJ == 8)
         return hipErrorInvalidValue;   // (as above: no room for the skip codes)
+    else if (fast == 2)
+        hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 0, 1, 2, CB, MULTI>), grid, block, 0, stream, a);
     else if (fast)
         hipLaunchKernelGGL((qconv_fx3_kernel<KIND, WC, NJ, 0, 1, 1, CB, MULTI>), grid, block, 0, stream, a);
     else
@@ -802,7 +814,7 @@ hipError_t launch3_modes(const MfmaArgs &a, bool fast, hipStream_t stream)
 }
 
 template <int KIND>
-hipError_t launch_kind(const MfmaArgs &a, const GfPlan &p, bool fast, hipStream_t stream)
+hipError_t launch_kind(const MfmaArgs &a, const GfPlan &p, int fast, hipStream_t stream)
 {
     if (p.kw < 0) {   // 3x3, stride 1: the input tile in LDS
         const int tile = p.mi * 10 + p.nj;
@@ -848,9 +860,9 @@ hipError_t launch_qconv_fx(const MfmaArgs &a, const GfPlan &p, hipStream_t strea
             (long long)a.seg[i].n * a.seg[i].h * a.seg[i].w * a.cin / (f6 ? 2 : 4) >= (1LL << 31) ||
             a.seg[i].P + 256 >= (1LL << 31))
             return hipErrorInvalidValue;
-    bool fast = true;
+    int fast = 2;
     for (int i = 0; i < a.nseg; ++i)
-        fast = fast && a.seg[i].fast;
+        fast = a.seg[i].fast < fast ? a.seg[i].fast : fast;
     return f6 ? launch_kind<GF_F6>(a, p, fast, stream) : launch_kind<GF_F4>(a, p, fast, stream);
 }
 

@@ -342,7 +342,6 @@ __global__ void __launch_bounds__(64 * KW, 2) qconv_gf_kernel(MfmaArgs A)
         }
         const v4i mult = *(const v4i *)(tab + 64 * EPI_MULT + 4 * q);
         const v4i shift = *(const v4i *)(tab + 64 * EPI_SHIFT + 4 * q);
-        const v4i rnd = *(const v4i *)(tab + 64 * EPI_RND + 4 * q);
 #pragma unroll
         for (int jj = 0; jj < JU; ++jj) {
             int kv[4] = {0, 0, 0, 0};
@@ -357,7 +356,13 @@ __global__ void __launch_bounds__(64 * KW, 2) qconv_gf_kernel(MfmaArgs A)
                     kv[e] = (int)((skw[jj][q] >> (e * A.skip_bits)) & ((1u << A.skip_bits) - 1));
             }
             uint32_t w = 0;
-            if (S.fast) {
+            if (EP == 1 && S.fast == 2) {   // the accumulator itself: the tables hold the bias and its unit
+                const v4i fa = *(const v4i *)(tab + 64 * EPI_FA + 4 * q), fb = *(const v4i *)(tab + 64 * EPI_FB + 4 * q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    w |= (uint32_t)quant_f32((float)fin[IG * jj + q][e], __int_as_float(fa[e]), __int_as_float(fb[e]),
+                                             (float)A.qmax) << (e * A.bits_out);
+            } else if (S.fast) {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     int u = v[jj][e];
@@ -365,7 +370,7 @@ __global__ void __launch_bounds__(64 * KW, 2) qconv_gf_kernel(MfmaArgs A)
                         const int scaled = rsm32(ss[e] ? u : kv[e], sc[e], sd[e]);
                         u = (int)((unsigned)scaled + (unsigned)(ss[e] ? kv[e] : u));
                     }
-                    int y = requant32(u, mult[e], (long long)rnd[e] << 32, shift[e] - 1);
+                    int y = requant32(u, mult[e], requant_rnd(shift[e]), shift[e] - 1);
                     y = y < 0 ? 0 : (y > A.qmax ? A.qmax : y);
                     w |= (uint32_t)y << (e * A.bits_out);
                 }

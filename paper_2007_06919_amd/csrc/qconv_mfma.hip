@@ -524,15 +524,14 @@ __global__ void __launch_bounds__(64 * WC * WP, (Cfg<BI, MI, NJ, WC, WP, OCC>::W
         static_for<MI>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
             const int cl = co_loc + 4 * i;
-            const int4 m4 = *(const int4 *)(prm + EPI_MULT * C::BCO + cl);
-            const int4 s4 = *(const int4 *)(prm + (FAST ? EPI_SHR : EPI_SHIFT) * C::BCO + cl);
+            const int4 m4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FB : EPI_MULT) * C::BCO + cl);
+            const int4 s4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FA : EPI_SHIFT) * C::BCO + cl);
             const int mult[4] = {m4.x, m4.y, m4.z, m4.w};
-            const int shf[4] = {s4.x, s4.y, s4.z, s4.w};
+            const int shf[4] = {s4.x - (FAST == 1), s4.y - (FAST == 1), s4.z - (FAST == 1), s4.w - (FAST == 1)};
             long long rnd[4] = {0, 0, 0, 0};  // 2^(shift-2) in the high word
-            if constexpr (FAST) {
-                const int4 r4 = *(const int4 *)(prm + EPI_RND * C::BCO + cl);
-                rnd[0] = (long long)r4.x << 32; rnd[1] = (long long)r4.y << 32;
-                rnd[2] = (long long)r4.z << 32; rnd[3] = (long long)r4.w << 32;
+            if constexpr (FAST == 1) {
+            rnd[0] = requant_rnd(s4.x); rnd[1] = requant_rnd(s4.y);
+            rnd[2] = requant_rnd(s4.z); rnd[3] = requant_rnd(s4.w);
             }
             int sc[4] = {0, 0, 0, 0}, sd[4] = {0, 0, 0, 0}, sside[4] = {0, 0, 0, 0};
             long long srnd[4] = {0, 0, 0, 0};  // rounding terms of the alignment
@@ -570,7 +569,12 @@ __global__ void __launch_bounds__(64 * WC * WP, (Cfg<BI, MI, NJ, WC, WP, OCC>::W
                 for (int e = 0; e < 4; ++e) {
                     const int v = acc[i][j][e];  // acc + bias
                     int y;
-                    if constexpr (FAST) {
+                    if constexpr (FAST == 2) {
+                        float b = __int_as_float(mult[e]);
+                        if constexpr (LUT)
+                            b = __int_as_float(lut_l[((4 * i + e) << BI) + kv[e]]);
+                        y = quant_f32((float)v, __int_as_float(shf[e]), b, (float)QMAX);
+                    } else if constexpr (FAST) {
                         int u = v;
                         // u fits in int32, so the sum modulo 2^32 is exact
                         if constexpr (LUT) {
@@ -629,9 +633,9 @@ __global__ void __launch_bounds__(64 * WC * WP, (Cfg<BI, MI, NJ, WC, WP, OCC>::W
             __syncthreads();  // staging is rewritten by the next pass
         });
     } else if constexpr (SKK == 1) {
-        if (use_lut)
+        if (FAST == 2 || use_lut)
             body(std::true_type{}, I0{}, INJ{});
-        else
+        else if constexpr (FAST != 2)
             body(std::false_type{}, I0{}, INJ{});
     } else {
         body(std::false_type{}, I0{}, INJ{});
@@ -969,15 +973,14 @@ __global__ void __launch_bounds__(256, 2) qconv_stream_kernel(MfmaArgs A)
             static_for<MI>([&](auto ic) {
                 constexpr int i = decltype(ic)::value;
                 const int cl = co_loc + 4 * i;
-                const int4 m4 = *(const int4 *)(prm + EPI_MULT * BCO + cl);
-                const int4 s4 = *(const int4 *)(prm + (FAST ? EPI_SHR : EPI_SHIFT) * BCO + cl);
+                const int4 m4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FB : EPI_MULT) * BCO + cl);
+                const int4 s4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FA : EPI_SHIFT) * BCO + cl);
                 const int mult[4] = {m4.x, m4.y, m4.z, m4.w};
-                const int shf[4] = {s4.x, s4.y, s4.z, s4.w};
+                const int shf[4] = {s4.x - (FAST == 1), s4.y - (FAST == 1), s4.z - (FAST == 1), s4.w - (FAST == 1)};
                 long long rnd[4] = {0, 0, 0, 0};
-                if constexpr (FAST) {
-                    const int4 r4 = *(const int4 *)(prm + EPI_RND * BCO + cl);
-                    rnd[0] = (long long)r4.x << 32; rnd[1] = (long long)r4.y << 32;
-                    rnd[2] = (long long)r4.z << 32; rnd[3] = (long long)r4.w << 32;
+                if constexpr (FAST == 1) {
+            rnd[0] = requant_rnd(s4.x); rnd[1] = requant_rnd(s4.y);
+            rnd[2] = requant_rnd(s4.z); rnd[3] = requant_rnd(s4.w);
                 }
                 int sc[4] = {0, 0, 0, 0}, sd[4] = {0, 0, 0, 0}, sside[4] = {0, 0, 0, 0};
                 long long srnd[4] = {0, 0, 0, 0};  // rounding terms of the alignment
@@ -1009,7 +1012,12 @@ __global__ void __launch_bounds__(256, 2) qconv_stream_kernel(MfmaArgs A)
                             return *(const int32_t *)((const uint8_t *)lds + a + ((4 * i + e) << (BI + 2)));
                         };
                         int y;
-                        if constexpr (FAST) {
+                        if constexpr (FAST == 2) {
+                            float b = __int_as_float(mult[e]);
+                            if constexpr (LUT)
+                                b = __int_as_float(lut_at());
+                            y = quant_f32((float)v, __int_as_float(shf[e]), b, (float)QMAX);
+                        } else if constexpr (FAST) {
                             int u = v;
                             // u fits in int32, so the sum modulo 2^32 is exact
                             if constexpr (LUT) {
@@ -1034,9 +1042,9 @@ __global__ void __launch_bounds__(256, 2) qconv_stream_kernel(MfmaArgs A)
                 });
             });
         };
-        if (use_lut)
-            body(std::true_type{});
-        else
+        if (FAST == 2 ? SKK == 1 : use_lut)
+            body(std::integral_constant<bool, SKK == 1>{});
+        else if constexpr (FAST != 2 || SKK != 1)
             body(std::false_type{});
         if (A.qmax == 7) {  // 3-bit codes (the epilogue clamped to 15)
 #pragma unroll
@@ -1056,9 +1064,15 @@ template <int BI, int MI, int NJ, int WC, int WP, int OUTK, int SKK, int OCC = 0
 hipError_t launch_t(const MfmaArgs &a, hipStream_t stream)
 {
     dim3 grid(8 * a.tiles_per_xcd), block(64 * WC * WP);
-    bool fast = true;
+    int fast = 2;
     for (int i = 0; i < a.nseg; ++i)
-        fast = fast && a.seg[i].fast;
+        fast = a.seg[i].fast < fast ? a.seg[i].fast : fast;
+    if constexpr (BI == 4 && OUTK == 0 && SKK != 2) {
+        if (fast == 2) {
+            hipLaunchKernelGGL((qconv_mfma_kernel<BI, MI, NJ, WC, WP, OUTK, SKK, 2, 0, OCC>), grid, block, 0, stream, a);
+            return hipGetLastError();
+        }
+    }
     if (OUTK == 1 || fast)
         hipLaunchKernelGGL((qconv_mfma_kernel<BI, MI, NJ, WC, WP, OUTK, SKK, 1, 0, OCC>), grid, block, 0, stream, a);
     else
@@ -1168,29 +1182,37 @@ hipError_t launch_qconv_stream(const MfmaArgs &a, hipStream_t stream)
     const int slots = (bco == 256 || hv) ? 512 : 768;
     const int nstream = qtiles < slots / a.co_tiles ? qtiles : slots / a.co_tiles;
     dim3 grid(nstream * a.co_tiles), block(256);
-    bool fast = true;
+    int fast = 2;
     for (int i = 0; i < a.nseg; ++i)
-        fast = fast && a.seg[i].fast;
+        fast = a.seg[i].fast < fast ? a.seg[i].fast : fast;
     if (hv) {
         if (a.skip_bits == 0) {
-            if (fast)
+            if (fast == 2)
+                hipLaunchKernelGGL((qconv_stream_kernel<0, 2, 4, 2, 1>), grid, block, 0, stream, a);
+            else if (fast)
                 hipLaunchKernelGGL((qconv_stream_kernel<0, 1, 4, 2, 1>), grid, block, 0, stream, a);
             else
                 hipLaunchKernelGGL((qconv_stream_kernel<0, 0, 4, 2, 1>), grid, block, 0, stream, a);
         } else {
-            if (fast)
+            if (fast == 2)
+                hipLaunchKernelGGL((qconv_stream_kernel<1, 2, 4, 2, 1>), grid, block, 0, stream, a);
+            else if (fast)
                 hipLaunchKernelGGL((qconv_stream_kernel<1, 1, 4, 2, 1>), grid, block, 0, stream, a);
             else
                 hipLaunchKernelGGL((qconv_stream_kernel<1, 0, 4, 2, 1>), grid, block, 0, stream, a);
         }
     } else if (bco != 256) {
         if (bco == 128) {
-            if (fast)
+            if (fast == 2)
+                hipLaunchKernelGGL((qconv_stream_kernel<0, 2, 4, 2>), grid, block, 0, stream, a);
+            else if (fast)
                 hipLaunchKernelGGL((qconv_stream_kernel<0, 1, 4, 2>), grid, block, 0, stream, a);
             else
                 hipLaunchKernelGGL((qconv_stream_kernel<0, 0, 4, 2>), grid, block, 0, stream, a);
         } else {
-            if (fast)
+            if (fast == 2)
+                hipLaunchKernelGGL((qconv_stream_kernel<0, 2, 4, 1>), grid, block, 0, stream, a);
+            else if (fast)
                 hipLaunchKernelGGL((qconv_stream_kernel<0, 1, 4, 1>), grid, block, 0, stream, a);
             else
                 hipLaunchKernelGGL((qconv_stream_kernel<0, 0, 4, 1>), grid, block, 0, stream, a);
@@ -1201,12 +1223,16 @@ hipError_t launch_qconv_stream(const MfmaArgs &a, hipStream_t stream)
         else
             hipLaunchKernelGGL((qconv_stream_kernel<2, 0>), grid, block, 0, stream, a);
     } else if (a.skip_bits == 0) {
-        if (fast)
+        if (fast == 2)
+            hipLaunchKernelGGL((qconv_stream_kernel<0, 2>), grid, block, 0, stream, a);
+        else if (fast)
             hipLaunchKernelGGL((qconv_stream_kernel<0, 1>), grid, block, 0, stream, a);
         else
             hipLaunchKernelGGL((qconv_stream_kernel<0, 0>), grid, block, 0, stream, a);
     } else {
-        if (fast)
+        if (fast == 2)
+            hipLaunchKernelGGL((qconv_stream_kernel<1, 2>), grid, block, 0, stream, a);
+        else if (fast)
             hipLaunchKernelGGL((qconv_stream_kernel<1, 1>), grid, block, 0, stream, a);
         else
             hipLaunchKernelGGL((qconv_stream_kernel<1, 0>), grid, block, 0, stream, a);

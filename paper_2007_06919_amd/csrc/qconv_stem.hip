@@ -192,8 +192,7 @@ __global__ void __launch_bounds__(256, 4) qconv_stem_kernel(MfmaArgs A)
             const int c = co_glob + 4 * i;
             const v4i bias = *(const v4i *)(epi + EPI_BIAS * cp + c);
             const v4i mult = *(const v4i *)(epi + EPI_MULT * cp + c);
-            const v4i shf = *(const v4i *)(epi + (FAST ? EPI_SHR : EPI_SHIFT) * cp + c);
-            const v4i rnd = *(const v4i *)(epi + EPI_RND * cp + c);
+            const v4i shf = *(const v4i *)(epi + EPI_SHIFT * cp + c);
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -201,7 +200,7 @@ __global__ void __launch_bounds__(256, 4) qconv_stem_kernel(MfmaArgs A)
                     const int v = acc[i][j][e] + bias[e];
                     int y;
                     if constexpr (FAST) {
-                        y = requant32(v, mult[e], (long long)rnd[e] << 32, shf[e]);
+                        y = requant32(v, mult[e], requant_rnd(shf[e]), shf[e] - 1);
                         y = y < 0 ? 0 : (y > QMAX ? QMAX : y);
                     } else {
                         y = (int)requant_clamp(v, mult[e], shf[e], QMAX);

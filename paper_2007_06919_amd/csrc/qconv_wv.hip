@@ -462,15 +462,14 @@ __global__ void __launch_bounds__(256, NJ == 8 ? 2 : NJ == 4 ? (SKK == 2 ? 2 : 3
         constexpr bool LUT = decltype(lut_c)::value;
         constexpr int i = decltype(ic)::value;
         const int cl = co_loc + 4 * i;
-        const int4 m4 = *(const int4 *)(prm + EPI_MULT * WV_BCO + cl);
-        const int4 s4 = *(const int4 *)(prm + (FAST ? EPI_SHR : EPI_SHIFT) * WV_BCO + cl);
+        const int4 m4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FB : EPI_MULT) * WV_BCO + cl);
+        const int4 s4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FA : EPI_SHIFT) * WV_BCO + cl);
         const int mult[4] = {m4.x, m4.y, m4.z, m4.w};
-        const int shf[4] = {s4.x, s4.y, s4.z, s4.w};
+        const int shf[4] = {s4.x - (FAST == 1), s4.y - (FAST == 1), s4.z - (FAST == 1), s4.w - (FAST == 1)};
         long long rnd[4] = {0, 0, 0, 0};  // 2^(shift-2) in the high word
-        if constexpr (FAST) {
-            const int4 r4 = *(const int4 *)(prm + EPI_RND * WV_BCO + cl);
-            rnd[0] = (long long)r4.x << 32; rnd[1] = (long long)r4.y << 32;
-            rnd[2] = (long long)r4.z << 32; rnd[3] = (long long)r4.w << 32;
+        if constexpr (FAST == 1) {
+            rnd[0] = requant_rnd(s4.x); rnd[1] = requant_rnd(s4.y);
+            rnd[2] = requant_rnd(s4.z); rnd[3] = requant_rnd(s4.w);
         }
         int sc[4] = {0, 0, 0, 0}, sd[4] = {0, 0, 0, 0}, sside[4] = {0, 0, 0, 0};
         long long srnd[4] = {0, 0, 0, 0};  // rounding terms of the alignment
@@ -495,7 +494,12 @@ __global__ void __launch_bounds__(256, NJ == 8 ? 2 : NJ == 4 ? (SKK == 2 ? 2 : 3
                 else if constexpr (SKK == 2)
                     kv = acc2[i][j][e];  // the projection's int32 output (Eq. 7-8: the skip)
                 int y;
-                if constexpr (FAST) {
+                if constexpr (FAST == 2) {
+                    float b = __int_as_float(mult[e]);
+                    if constexpr (LUT)
+                        b = __int_as_float(lut_l[((4 * i + e) << BI) + kv]);
+                    y = quant_f32((float)v, __int_as_float(shf[e]), b, (float)QMAX);
+                } else if constexpr (FAST) {
                     int u = v;
                     // u fits in int32, so sums modulo 2^32 are exact
                     if constexpr (LUT) {
@@ -520,9 +524,9 @@ __global__ void __launch_bounds__(256, NJ == 8 ? 2 : NJ == 4 ? (SKK == 2 ? 2 : 3
         }
     };
     auto body = [&](auto lut_c) { static_for<MI>([&](auto ic) { group(lut_c, ic, 0, NJ); }); };
-    if (use_lut)
-        body(std::true_type{});
-    else
+    if (FAST == 2 ? SKK == 1 : use_lut)
+        body(std::integral_constant<bool, SKK == 1>{});
+    else if constexpr (FAST != 2 || SKK != 1)
         body(std::false_type{});
     if (OUTK == 0 && A.qmax == 7) {  // 3-bit codes (the epilogue clamped to 15)
 #pragma unroll
@@ -580,7 +584,7 @@ __global__ void __launch_bounds__(256, NJ == 8 ? 2 : NJ == 4 ? (SKK == 2 ? 2 : 3
 }
 
 template <int NJ>
-void launch_wv_modes(const MfmaArgs &a, bool fast, dim3 grid, hipStream_t stream)
+void launch_wv_modes(const MfmaArgs &a, int fast, dim3 grid, hipStream_t stream)
 {
     const dim3 block(256);
     if constexpr (NJ == 8) {
@@ -595,12 +599,16 @@ void launch_wv_modes(const MfmaArgs &a, bool fast, dim3 grid, hipStream_t stream
         else
             hipLaunchKernelGGL((qconv_wv_kernel<2, 0, 0, NJ>), grid, block, 0, stream, a);
     } else if (a.skip_bits == 0) {
-        if (fast)
+        if (fast == 2)
+            hipLaunchKernelGGL((qconv_wv_kernel<0, 0, 2, NJ>), grid, block, 0, stream, a);
+        else if (fast)
             hipLaunchKernelGGL((qconv_wv_kernel<0, 0, 1, NJ>), grid, block, 0, stream, a);
         else
             hipLaunchKernelGGL((qconv_wv_kernel<0, 0, 0, NJ>), grid, block, 0, stream, a);
     } else {
-        if (fast)
+        if (fast == 2)
+            hipLaunchKernelGGL((qconv_wv_kernel<0, 1, 2, NJ>), grid, block, 0, stream, a);
+        else if (fast)
             hipLaunchKernelGGL((qconv_wv_kernel<0, 1, 1, NJ>), grid, block, 0, stream, a);
         else
             hipLaunchKernelGGL((qconv_wv_kernel<0, 1, 0, NJ>), grid, block, 0, stream, a);
@@ -645,9 +653,9 @@ hipError_t launch_qconv_wv(const MfmaArgs &a, hipStream_t stream)
             (long long)a.co_tiles * a.ksteps * WV_BCO * KC >= (1LL << 31))
             return hipErrorInvalidValue;
     const dim3 grid(8 * a.tiles_per_xcd);
-    bool fast = true;
+    int fast = 2;
     for (int i = 0; i < a.nseg; ++i)
-        fast = fast && a.seg[i].fast;
+        fast = a.seg[i].fast < fast ? a.seg[i].fast : fast;
     if (wide)
         launch_wv_modes<9>(a, fast, grid, stream);
     else if (narrow)

@@ -262,15 +262,14 @@ __global__ void __launch_bounds__(256, 2) qconv_wvs_kernel(MfmaArgs A)
             constexpr bool LUT = decltype(lut_c)::value;
             constexpr int i = decltype(ic)::value;
             const int cl = co_loc + 4 * i;
-            const int4 m4 = *(const int4 *)(prm + EPI_MULT * WS_BCO + cl);
-            const int4 s4 = *(const int4 *)(prm + (FAST ? EPI_SHR : EPI_SHIFT) * WS_BCO + cl);
+            const int4 m4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FB : EPI_MULT) * WS_BCO + cl);
+            const int4 s4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FA : EPI_SHIFT) * WS_BCO + cl);
             const int mult[4] = {m4.x, m4.y, m4.z, m4.w};
-            const int shf[4] = {s4.x, s4.y, s4.z, s4.w};
+            const int shf[4] = {s4.x - (FAST == 1), s4.y - (FAST == 1), s4.z - (FAST == 1), s4.w - (FAST == 1)};
             long long rnd[4] = {0, 0, 0, 0};  // 2^(shift-2) in the high word
-            if constexpr (FAST) {
-                const int4 r4 = *(const int4 *)(prm + EPI_RND * WS_BCO + cl);
-                rnd[0] = (long long)r4.x << 32; rnd[1] = (long long)r4.y << 32;
-                rnd[2] = (long long)r4.z << 32; rnd[3] = (long long)r4.w << 32;
+            if constexpr (FAST == 1) {
+            rnd[0] = requant_rnd(s4.x); rnd[1] = requant_rnd(s4.y);
+            rnd[2] = requant_rnd(s4.z); rnd[3] = requant_rnd(s4.w);
             }
             int sc[4] = {0, 0, 0, 0}, sd[4] = {0, 0, 0, 0}, sside[4] = {0, 0, 0, 0};
             long long srnd[4] = {0, 0, 0, 0};  // rounding terms of the alignment
@@ -293,7 +292,12 @@ __global__ void __launch_bounds__(256, 2) qconv_wvs_kernel(MfmaArgs A)
                     if constexpr (SKK == 1)
                         kv = (int)__builtin_amdgcn_ubfe(skw[j][bit >> 5], bit & 31, BI);
                     int y;
-                    if constexpr (FAST) {
+                    if constexpr (FAST == 2) {
+                        float b = __int_as_float(mult[e]);
+                        if constexpr (LUT)
+                            b = __int_as_float(lut_l[((4 * i + e) << BI) + kv]);
+                        y = quant_f32((float)v, __int_as_float(shf[e]), b, (float)QMAX);
+                    } else if constexpr (FAST) {
                         int u = v;
                         // u fits in int32, so sums modulo 2^32 are exact
                         if constexpr (LUT) {
@@ -317,9 +321,9 @@ __global__ void __launch_bounds__(256, 2) qconv_wvs_kernel(MfmaArgs A)
                 }
             }
         };
-        if (use_lut)
-            static_for<MI>([&](auto ic) { group(std::true_type{}, ic); });
-        else
+        if (FAST == 2 ? SKK == 1 : use_lut)
+            static_for<MI>([&](auto ic) { group(std::integral_constant<bool, SKK == 1>{}, ic); });
+        else if constexpr (FAST != 2 || SKK != 1)
             static_for<MI>([&](auto ic) { group(std::false_type{}, ic); });
         if (A.qmax == 7) {  // 3-bit codes (the epilogue clamped to 15)
 #pragma unroll
@@ -356,16 +360,20 @@ __global__ void __launch_bounds__(256, 2) qconv_wvs_kernel(MfmaArgs A)
 }
 
 template <int NST>
-void launch_wvs_modes(const MfmaArgs &a, bool fast, dim3 grid, hipStream_t stream)
+void launch_wvs_modes(const MfmaArgs &a, int fast, dim3 grid, hipStream_t stream)
 {
     const dim3 block(256);
     if (a.skip_bits == 0) {
-        if (fast)
+        if (fast == 2)
+            hipLaunchKernelGGL((qconv_wvs_kernel<NST, 0, 2>), grid, block, 0, stream, a);
+        else if (fast)
             hipLaunchKernelGGL((qconv_wvs_kernel<NST, 0, 1>), grid, block, 0, stream, a);
         else
             hipLaunchKernelGGL((qconv_wvs_kernel<NST, 0, 0>), grid, block, 0, stream, a);
     } else {
-        if (fast)
+        if (fast == 2)
+            hipLaunchKernelGGL((qconv_wvs_kernel<NST, 1, 2>), grid, block, 0, stream, a);
+        else if (fast)
             hipLaunchKernelGGL((qconv_wvs_kernel<NST, 1, 1>), grid, block, 0, stream, a);
         else
             hipLaunchKernelGGL((qconv_wvs_kernel<NST, 1, 0>), grid, block, 0, stream, a);
