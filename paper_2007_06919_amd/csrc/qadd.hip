@@ -72,13 +72,15 @@ __global__ void __launch_bounds__(256) channel_sums_kernel(const int32_t *v, lon
 // The same with 16-byte loads, for channel counts that are a multiple of 4 and a
 // 16-byte aligned tensor. One thread per channel walks its rows one load after
 // another, with too few rows in flight to reach the memory's rate (16700 x 256:
-// 71 us, 0.24 TB/s); here a thread takes 4 channels of every fourth row of the
-// strip, four rows in flight, the four row groups are added in LDS, and the strips
-// are short enough to fill the chip (9 us).
-__global__ void __launch_bounds__(256) channel_sums4_kernel(const int32_t *v, long long rows, int c,
-                                                           long long rows_per_block, long long *sums)
+// 71 us, 0.24 TB/s). Here a thread takes 4 channels of every 16th row of the strip,
+// four rows in flight, and the sixteen row groups are added in LDS. The strips'
+// atomics then set the pace (512 strips of 4 row groups: 47 us), so there are few
+// strips, each on a workgroup of 16 waves.
+constexpr int CS_TY = 16;
+__global__ void __launch_bounds__(64 * CS_TY) channel_sums4_kernel(const int32_t *v, long long rows, int c,
+                                                                  long long rows_per_block, long long *sums)
 {
-    __shared__ long long part[3][64][8];
+    __shared__ long long part[CS_TY][64][2];
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     const int ch = (blockIdx.x * 64 + tx) * 4;
     const long long r0 = (long long)blockIdx.y * rows_per_block;
@@ -95,29 +97,31 @@ __global__ void __launch_bounds__(256) channel_sums4_kernel(const int32_t *v, lo
     if (ch < c) {
         const int32_t *p = v + ch;
         long long r = r0 + ty;
-        for (; r + 12 < r1; r += 16) {
+        for (; r + 3 * CS_TY < r1; r += 4 * CS_TY) {
             int4 x[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k)
-                x[k] = *(const int4 *)(p + (r + 4 * k) * c);
+                x[k] = *(const int4 *)(p + (r + k * CS_TY) * c);
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 add(x[k]);
         }
-        for (; r < r1; r += 4)
+        for (; r < r1; r += CS_TY)
             add(*(const int4 *)(p + r * c));
     }
-    if (ty > 0) {
+    // channel k of each four: row group 0 adds up the sums, row group 1 the squares
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            part[ty - 1][tx][k] = s[k];
-    }
-    __syncthreads();
-    if (ty == 0 && ch < c) {
+    for (int k = 0; k < 4; ++k) {
+        __syncthreads();
+        part[ty][tx][0] = s[k];
+        part[ty][tx][1] = s[4 + k];
+        __syncthreads();
+        if (ty < 2 && ch < c) {
+            long long t = 0;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const long long t = s[k] + part[0][tx][k] + part[1][tx][k] + part[2][tx][k];
-            atomicAdd((unsigned long long *)&sums[(k < 4 ? 0 : c) + ch + (k & 3)], (unsigned long long)t);
+            for (int y = 0; y < CS_TY; ++y)
+                t += part[y][tx][ty];
+            atomicAdd((unsigned long long *)&sums[ty * c + ch + k], (unsigned long long)t);
         }
     }
 }
@@ -142,14 +146,12 @@ hipError_t launch_channel_sums(const int32_t *v, long long rows, int c, long lon
     if (rows == 0)
         return hipSuccess;
     if (c % 4 == 0 && ((uintptr_t)v & 15) == 0) {
-        // about 1024 workgroups, strips of 32 rows or more (the atomics of a strip
-        // cost about as much as a few rows)
         const int gx = (c / 4 + 63) / 64;
-        const long long strips = 1024 / gx > 0 ? 1024 / gx : 1;
+        const long long strips = 96 / gx > 8 ? 96 / gx : 8;
         long long per = (rows + strips - 1) / strips;
-        per = per < 32 ? 32 : per;
-        hipLaunchKernelGGL(channel_sums4_kernel, dim3(gx, (unsigned)((rows + per - 1) / per)), dim3(256), 0, stream, v,
-                           rows, c, per, sums);
+        per = per < 64 ? 64 : per;
+        hipLaunchKernelGGL(channel_sums4_kernel, dim3(gx, (unsigned)((rows + per - 1) / per)), dim3(64 * CS_TY), 0,
+                           stream, v, rows, c, per, sums);
         return hipGetLastError();
     }
     // at most 4096 row strips (grid.y limit is 65535)
