@@ -51,16 +51,37 @@ constexpr int fx_epilogue_bytes()
     return OUTK == 1 || outb > tabs ? outb : tabs;
 }
 
+// With fp32 requantisation and no skip the epilogue reads two numbers per channel:
+// their copy to LDS (2 x 64 WC words at ftab) starts with the kernel and has long
+// landed by the end of the K loop, where loading the tables would keep the tile's
+// waves waiting twice (3x3 256 -> 256 on 267200 pixels: 88.8 -> 86.5 us, 128 ->
+// 128 on 133600: 21.2 -> 20.0). Every lane
+// waits for later loads of its own before the barrier that follows.
+template <int WC>
+__device__ __forceinline__ void fx_early_table(const MfmaArgs &A, const MfmaSeg &S, const int32_t *ftab, int co_tile,
+                                               int tid)
+{
+    static_assert(EPI_FB == EPI_FA + 1, "fields in order");
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (wave < 2 && lane < 16 * WC) {
+        // (a partial last channel tile: the table's own last channels again)
+        const int c = min(co_tile * (WC * 64) + 4 * lane, A.cout_pad - 4);
+        dma16(S.epi + (EPI_FA + wave) * A.cout_pad + c, lds_addr(ftab) + wave * (WC * 256));
+    }
+}
+
 // The epilogue of both tiled kernels: accumulators -> outputs. pixel(p): output
 // pixel of the tile's pixel p (wave wp's column j: pixels 16 (NJ wp + j) + r), or
-// -1. lds: fx_epilogue_bytes, free once every wave has arrived here.
+// -1. lds: fx_epilogue_bytes, free once every wave has arrived here. ftab: a and b of
+// the tile's channels (fx_early_table), where the epilogue needs no other table.
 template <int KIND, int WC, int NJ, int OUTK, int SKK, int FAST, typename PX>
-__device__ __forceinline__ void fx_epilogue(const MfmaArgs &A, const MfmaSeg &S, uint8_t *lds, v4f (&acc)[4][NJ],
-                                            const int co_tile, const int tid, PX &&pixel)
+__device__ __forceinline__ void fx_epilogue(const MfmaArgs &A, const MfmaSeg &S, uint8_t *lds, const int32_t *ftab,
+                                            v4f (&acc)[4][NJ], const int co_tile, const int tid, PX &&pixel)
 {
     constexpr bool F6 = KIND == GF_F6;
     constexpr int MI = 4, BPX = 16 * NJ * (4 / WC);
     constexpr int BO = F6 ? 4 : 2, QMAX = (1 << BO) - 1;   // output code width
+    constexpr bool EARLY = FAST == 2 && SKK == 0;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wc = wave % WC, wp = wave / WC, r = lane & 15, g = lane >> 4;
     const int pw = 16 * NJ * wp + r;
@@ -131,20 +152,22 @@ __device__ __forceinline__ void fx_epilogue(const MfmaArgs &A, const MfmaSeg &S,
             }
         }
     }
-    __syncthreads();   // every wave is done with the ring
     // the tables of the tile's channels, and of side-0 skips RSM(k, c, d) per code
     int32_t *prm = (int32_t *)lds;                   // [EPI_FIELDS][WC * 64]
     int32_t *lut = prm + EPI_FIELDS * WC * 64;       // [WC * 64][QMAX + 1]
     const bool use_lut = SKK == 1 && S.side0;
-    for (int u = tid; u < EPI_FIELDS * WC * 64; u += 256) {
-        const int f = u / (WC * 64), c = u % (WC * 64);
-        prm[u] = co_tile * (WC * 64) + c < A.cout_pad ? S.epi[f * A.cout_pad + co_tile * (WC * 64) + c] : 0;
+    if constexpr (!EARLY) {
+        __syncthreads();   // every wave is done with the ring
+        for (int u = tid; u < EPI_FIELDS * WC * 64; u += 256) {
+            const int f = u / (WC * 64), c = u % (WC * 64);
+            prm[u] = co_tile * (WC * 64) + c < A.cout_pad ? S.epi[f * A.cout_pad + co_tile * (WC * 64) + c] : 0;
+        }
+        if (use_lut)
+            for (int u = tid; u < WC * 64 * (QMAX + 1); u += 256)
+                lut[u] = co_tile * (WC * 64) + u / (QMAX + 1) < A.cout
+                             ? S.lut[(long long)co_tile * (WC * 64) * (QMAX + 1) + u] : 0;
+        __syncthreads();
     }
-    if (use_lut)
-        for (int u = tid; u < WC * 64 * (QMAX + 1); u += 256)
-            lut[u] = co_tile * (WC * 64) + u / (QMAX + 1) < A.cout
-                         ? S.lut[(long long)co_tile * (WC * 64) * (QMAX + 1) + u] : 0;
-    __syncthreads();
     uint32_t outw[NJ][OW];
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
@@ -156,8 +179,10 @@ __device__ __forceinline__ void fx_epilogue(const MfmaArgs &A, const MfmaSeg &S,
     auto group = [&](auto lut_c, auto ic) {
         constexpr bool LUT = decltype(lut_c)::value;
         constexpr int i = decltype(ic)::value;
-        const int32_t *tab = prm + cl + 4 * i;
-        const v4i bias = *(const v4i *)(tab + EPI_BIAS * WC * 64);
+        const int32_t *tab = (EARLY ? ftab - EPI_FA * WC * 64 : prm) + cl + 4 * i;
+        v4i bias = {0, 0, 0, 0};
+        if constexpr (FAST != 2)
+            bias = *(const v4i *)(tab + EPI_BIAS * WC * 64);
         const v4i mult = *(const v4i *)(tab + (FAST == 2 ? EPI_FB : EPI_MULT) * WC * 64);
         const v4i shf = *(const v4i *)(tab + (FAST == 2 ? EPI_FA : EPI_SHIFT) * WC * 64);
         v4i sc = {0, 0, 0, 0}, sd = sc, ss = sc;
@@ -276,7 +301,9 @@ __global__ void __launch_bounds__(256, OCC) qconv_fx_kernel(MfmaArgs A)
     constexpr int XROW = 128, YROW = F6 ? 64 : 0;    // LDS bytes of a pixel and stage
     constexpr int STAGE = BPX * (XROW + YROW);
     constexpr int EPIB = fx_epilogue_bytes<KIND, WC, NJ, OUTK, SKK>();
-    constexpr int LDS = 2 * STAGE > EPIB ? 2 * STAGE : EPIB;
+    constexpr bool EARLY = FAST == 2 && SKK == 0 && OUTK == 0;
+    constexpr int OFF_F = 2 * STAGE > EPIB ? 2 * STAGE : EPIB;
+    constexpr int LDS = OFF_F + (EARLY ? 2 * WC * 256 : 0);
     constexpr int RA = NJ >= 8 ? 2 : 1;              // fragments are read RA column tiles ahead
     static_assert(NJ >= 4 && NPC >= 2 && NPC <= 8, "tile");
     __shared__ __attribute__((aligned(1024))) uint8_t lds[LDS];
@@ -305,6 +332,9 @@ __global__ void __launch_bounds__(256, OCC) qconv_fx_kernel(MfmaArgs A)
     const int KS = A.ksteps;                         // K steps (of 128 channels)
     const int NST = (KS + 1) / 2;
     const int hw = S.ho * S.wo;
+    const int32_t *const ftab = (const int32_t *)(lds + OFF_F % LDS);
+    if constexpr (EARLY)
+        fx_early_table<WC>(A, S, ftab, co_tile, tid);
 
     // ---- activation copies: piece m of a stage = pixels 32m .. 32m+31 of the
     // tile, lane tid copying chunk tid % 8 of the stage for pixel 32m + tid / 8;
@@ -504,7 +534,7 @@ __global__ void __launch_bounds__(256, OCC) qconv_fx_kernel(MfmaArgs A)
         buf ^= STAGE;
     }
 
-    fx_epilogue<KIND, WC, NJ, OUTK, SKK, FAST>(A, S, lds, acc, co_tile, tid, [&](int p) -> long long {
+    fx_epilogue<KIND, WC, NJ, OUTK, SKK, FAST>(A, S, lds, ftab, acc, co_tile, tid, [&](int p) -> long long {
         const long long px = (long long)px_tile * BPX + p;
         return px < S.P ? px : -1;
     });
@@ -543,7 +573,9 @@ __global__ void __launch_bounds__(256, 2) qconv_fx3_kernel(MfmaArgs A)
     constexpr int TAB = (NPX * 4 + 127) / 128 * 128;
     constexpr int DATA = NPX * (XROW + YROW);
     constexpr int EPIB = fx_epilogue_bytes<KIND, WC, NJ, OUTK, SKK>();
-    constexpr int LDS = TAB + (DATA > EPIB ? DATA : EPIB);
+    constexpr bool EARLY = FAST == 2 && SKK == 0 && OUTK == 0;
+    constexpr int OFF_F = TAB + (DATA > EPIB ? (DATA + 15) / 16 * 16 : EPIB);
+    constexpr int LDS = OFF_F + (EARLY ? 2 * WC * 256 : 0);
     constexpr int PPI = 256 / CB, IT = (NPX + PPI - 1) / PPI;   // pixels per copy pass, passes
     constexpr int RA = NJ >= 8 ? 2 : 1;
     static_assert(CB == 8 || CB == 4 || CB == 2, "chunks per block");
@@ -572,6 +604,9 @@ __global__ void __launch_bounds__(256, 2) qconv_fx3_kernel(MfmaArgs A)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wc = wave % WC, wp = wave / WC;
     const int r = lane & 15, g = lane >> 4;
+    const int32_t *const ftab = (const int32_t *)(lds + OFF_F % LDS);
+    if constexpr (EARLY)
+        fx_early_table<WC>(A, S, ftab, co_tile, tid);
     const int KS = A.ksteps, kpt = CB == 2 ? 1 : A.cin / 128;   // K steps, per tap
     const int nblk = MULTI ? A.cin / (32 * CB) : 1;
     const int row_bytes = A.cin * XB / 32;
@@ -760,7 +795,7 @@ __global__ void __launch_bounds__(256, 2) qconv_fx3_kernel(MfmaArgs A)
     }
     // (the thread's number from its lane, so that none is held through the K loop)
     const int tid2 = 64 * wave + (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-    fx_epilogue<KIND, WC, NJ, OUTK, SKK, FAST>(A, S, data, acc, co_tile, tid2, [&](int p) -> long long {
+    fx_epilogue<KIND, WC, NJ, OUTK, SKK, FAST>(A, S, data, ftab, acc, co_tile, tid2, [&](int p) -> long long {
         return tab[RUN + 1 + p];
     });
 }
