@@ -1128,14 +1128,16 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
         // give every SIMD two waves; very few tiles are halved as well. 3x3 128 ->
         // 128 P 16700 (522 tiles), 1 / 2 / 4 waves: 9.9 / 9.1 / 11.1 us; 3x3 64 -> 64
         // P 66800 (1044): 10.0 / 12.3 / 13.1; 3x3 256 -> 256 P 4200 (264): 12.7 / 12.7 /
-        // 11.3; 3x3 stride 2 256 -> 256 P 77 (8): 11.9 / 8.1 / 7.2, halved 6.1
-        *plan = GfPlan{h0.gf_kind, 4, t64 <= 100 ? 2 : 4, t64 > 1000 ? 1 : t64 > 400 ? 2 : 4};
+        // 11.3; 3x3 stride 2 256 -> 256 P 77 (8): 11.9 / 8.1 / 7.2, halved 6.2, quartered
+        // 5.2; 2048 -> 256 P 273 (20) 28.2, 20.7, 15.8; 3x3 256 -> 256 P 1050 (68): 7.8, 6.5,
+        // 7.4
+        *plan = GfPlan{h0.gf_kind, t64 <= 64 && steps >= 4 ? 2 : 4, t64 <= 100 ? 2 : 4, t64 > 1000 ? 1 : t64 > 400 ? 2 : 4};
         if (cout <= 4)   // one row tile holds every channel
             *plan = GfPlan{h0.gf_kind, 1, 4, 4};
         else if (steps < plan->kw)
             plan->kw = steps < 2 ? 1 : 2;
     }
-    const int groups = wc ? (h0.gf_groups + wc - 1) / wc : plan->mi == 1 ? 1 : h0.gf_groups;
+    const int groups = wc ? (h0.gf_groups + wc - 1) / wc : cout <= 4 ? 1 : h0.gf_groups * (4 / plan->mi);
     const int px = wc ? 16 * nj * (4 / wc) : 16 * plan->nj;
     MfmaArgs &a = *out;
     a = MfmaArgs{};

@@ -459,6 +459,7 @@ hipError_t launch_kind(const MfmaArgs &a, const GfPlan &p, hipStream_t stream)
     case 422: return launch_ep<KIND, 4, 2, 2>(a, stream);
     case 424: return launch_ep<KIND, 4, 2, 4>(a, stream);
     case 144: return launch_ep<KIND, 1, 4, 4>(a, stream);
+    case 224: return launch_ep<KIND, 2, 2, 4>(a, stream);
     }
     return hipErrorInvalidValue;
 }

@@ -1,7 +1,7 @@
 """Parity of the global-fed kernel (operands straight from global memory, the
 waves of a tile splitting its K range) against the oracle, bit for bit: every
-tile and split its rule picks (64 x 64 tiles on 1, 2 and 4 waves, 64 x 32 on
-4, 16 channels x 64 pixels for at most 4 channels), the three operand formats,
+tile and split its rule picks (64 x 64 tiles on 1, 2 and 4 waves, 64 x 32 and
+32 x 32 on 4, 16 channels x 64 pixels for at most 4 channels), the three operand formats,
 every output and skip width, steps that span taps, partial channel groups and
 pixel tiles, and sums at the bound where fp32 stops being exact."""
 import numpy as np
@@ -21,8 +21,9 @@ def torch():
 
 
 CASES = {
-    # <= 100 tiles: 64 x 32, 4 waves
+    # <= 64 tiles of 64 x 64: 32 x 32, <= 100: 64 x 32 (the second case), 4 waves
     "f6_k5_two_taps_a_step": dict(n=1, h=32, w=32, cin=64, cout=64, k=3),
+    "f6_64x32": dict(n=1, h=25, w=42, cin=256, cout=256, k=3, skip_bits=4, wenc=1),
     "f6_up2_skip": dict(n=2, h=13, w=21, cin=256, cout=256, k=3, skip_bits=4, skip_up2=True, wenc=1),
     "f6_cin96_partial_group_int32": dict(n=1, h=9, w=11, cin=96, cout=80, k=3, stride=2, bits_out=32, wenc=1),
     "f6_cin32_one_step": dict(n=1, h=9, w=11, cin=32, cout=36, k=1, bits_out=32),
