@@ -410,7 +410,7 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     const int BLK_CO = h.blk_co;
     h.co_tiles = mfma ? (d.cout + BLK_CO - 1) / BLK_CO : 1;
     h.cout_pad = mfma ? h.co_tiles * BLK_CO : d.cout;
-    h.ksteps = stem ? 3 : mfma ? taps * (d.cin / KC) : 0;
+    h.ksteps = stem ? 4 : mfma ? taps * (d.cin / KC) : 0;
     h.fast.assign(d.num_levels, 0);
     h.gf_fast.assign(d.num_levels, 0);
     h.side0.assign(d.num_levels, 0);
@@ -429,21 +429,21 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
 
     std::vector<uint8_t> wbuf;
     if (stem) {
-        // [co_tile][K step][row rho][64 B]: K byte k = window row k / 24, tap
-        // (k % 24) / 3, channel k % 3 for k % 24 < 21, else zero; channel
-        // tile_row_channel(rho) of the 64-channel tile
-        wbuf.assign((size_t)h.co_tiles * 3 * 64 * KC, 0);
+        // [co_tile][K step][row tile][lane][16 B], lane = 16 (16-byte column) + row:
+        // K byte k = window row k / 32, tap k % 32 / 4, channel k % 4 (else zero);
+        // channel tile_row_channel(rho) of the 64-channel tile
+        wbuf.assign((size_t)h.co_tiles * 4 * 64 * KC, 0);
         for (int ct = 0; ct < h.co_tiles; ++ct)
             for (int rho = 0; rho < 64; ++rho) {
                 const int co = ct * 64 + tile_row_channel(rho, cpl);
-                for (int k = 0; k < 168; ++k) {
-                    const int kh = k / 24, rem = k % 24;
-                    if (rem >= 21)
-                        continue;
-                    const int kw = rem / 3, c = rem % 3;
-                    wbuf[(((size_t)ct * 3 + k / KC) * 64 + rho) * KC + k % KC] =
-                        (uint8_t)(int8_t)wv[((size_t)co * taps + kh * 7 + kw) * d.cin + c];
-                }
+                for (int kh = 0; kh < 7; ++kh)
+                    for (int kw = 0; kw < 7; ++kw)
+                        for (int c = 0; c < 3; ++c) {
+                            const int k = 32 * kh + 4 * kw + c;
+                            const int lane = k % KC / 16 * 16 + rho % 16;
+                            wbuf[((((size_t)ct * 4 + k / KC) * 4 + rho / 16) * 64 + lane) * 16 + k % 16] =
+                                (uint8_t)(int8_t)wv[((size_t)co * taps + kh * 7 + kw) * d.cin + c];
+                        }
             }
     } else if (fp4) {
         // tiles [co_tile][128-channel K step][row rho][64 bytes]: channel
@@ -987,12 +987,15 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
         m.side0 = s.conv->side0[s.level];
         m.lut = s.conv->lut_dev ? s.conv->lut_dev + (size_t)s.level * s.conv->cout_pad * (1 << h0.d.skip_bits)
                                 : nullptr;
-        const long long px_tiles = (m.P + blk_px - 1) / blk_px;
-        REQUIRE(tiles + px_tiles * co_tiles < (1LL << 26), "too many tiles for one launch");
+        // (the stem's tiles lie in one image each, and its grid does not grow with them)
+        const bool stem = tile_cfg == TILE_STEM;
+        const long long px_tiles = stem ? (long long)m.n * ((m.ho + STEM_TH - 1) / STEM_TH) * ((m.wo + STEM_TW - 1) / STEM_TW)
+                                        : (m.P + blk_px - 1) / blk_px;
+        REQUIRE(tiles + px_tiles * co_tiles < (1LL << (stem ? 30 : 26)), "too many tiles for one launch");
         tiles += (int)(px_tiles * co_tiles);
     }
-    // fp32 requantisation when every segment has it (4-bit codes in and out)
-    bool f32 = h0.d.bits_in == 4 && h0.d.out_mode == AQD_OUT_CODES && h0.d.bits_out == 4 && h0.d.skip_bits <= 4;
+    // fp32 requantisation when every segment has it (4-bit codes in and out, the stem)
+    bool f32 = (h0.d.bits_in == 4 || tile_cfg == TILE_STEM) && h0.d.out_mode == AQD_OUT_CODES && h0.d.bits_out == 4 && h0.d.skip_bits <= 4;
     for (int i = 0; i < a.nseg; ++i)
         f32 = f32 && a.seg[i].fast == 2;
     const size_t lut_words = (size_t)h0.cout_pad * (1 << (h0.d.skip_bits & 15));

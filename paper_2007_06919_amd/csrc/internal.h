@@ -35,8 +35,8 @@ enum { TILE_256x128 = 0, TILE_128x256 = 1, TILE_64x512 = 2,
        // 8-bit codes, cin a multiple of 128, int32 outputs: 256 x 128 tiles on
        // the int8 MFMA (qconv_b16.hip), weights in channel order at create
        TILE_B8 = 13,
-       // the 7x7 stride-2 stem on a 3-channel 8-bit image: 64 x 128 tiles, K =
-       // the whole window (qconv_stem.hip)
+       // the 7x7 stride-2 stem on a 3-channel 8-bit image: 64 channels x 8 rows
+       // of 32 pixels, K = the whole window (qconv_stem.hip)
        TILE_STEM = 14,
        // TILE_WV's kernel on 256 x 144 tiles, one workgroup per CU: code
        // outputs of launches a little above one round of 256 x 128 tiles
@@ -137,7 +137,9 @@ struct GfPlan {
 // seg.side0 as for the other kernels)
 hipError_t launch_qconv_fx(const MfmaArgs &a, const GfPlan &p, hipStream_t stream);
 hipError_t launch_qconv_gf(const MfmaArgs &a, const GfPlan &p, hipStream_t stream);
-// TILE_STEM launches (qconv_stem.hip); weights [co_tile][3][64 rows][64 B]
+// TILE_STEM launches (qconv_stem.hip); weights [co_tile][4][4][64 lanes][16 B]; tiles of
+// STEM_TH rows of STEM_TW output pixels of one image
+constexpr int STEM_TW = 32, STEM_TH = 8;
 hipError_t launch_qconv_stem(const MfmaArgs &a, hipStream_t stream);
 
 // ---- split-K combine + epilogue (qconv_splitk.hip) ---------------------------

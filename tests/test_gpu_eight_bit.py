@@ -127,6 +127,22 @@ def test_stem_on_mfma(torch, case):
         assert_same(got, oracle_conv(c, level), f"stem {variant} {case} level {level}")
 
 
+# edges of the stem's tiles (8 rows of 32 output pixels): one pixel, one short of a
+# tile, a tile, one more; images whose ends fall in one another's tiles; two tiles
+# of channels; a workgroup with several tiles
+STEM_EDGES = [(1, 1, 1, 64, 4), (5, 1, 2, 64, 4), (2, 15, 61, 64, 4), (1, 16, 64, 128, 4), (2, 17, 65, 64, 4),
+              (3, 18, 66, 128, 32), (3, 230, 770, 64, 4), (2, 230, 770, 128, 4)]
+
+
+@pytest.mark.parametrize("case", STEM_EDGES, ids=lambda c: "x".join(map(str, c)))
+def test_stem_tile_edges(torch, case):
+    n, h, w, cout, bo = case
+    c = _case(n + h + w, n, h, w, 3, cout, 7, 2, 8, 8, TWOS, bo)
+    assert _path(c) == "i8-mfma"
+    for level, got in enumerate(gpu_conv(c, torch)):
+        assert_same(got, oracle_conv(c, level), f"stem {case} level {level}")
+
+
 def test_aqd_full_retinanet_scaled(torch):
     """The fully quantized RetinaNet-R50 (8-bit image, stem and prediction
     convolutions, max-pooling, 4-bit elsewhere), calibrated: every tensor and
