@@ -417,6 +417,12 @@ def test_stream_grouped_segments(torch):
     (4, 5, 1, 2, (1, 9, 8, 6)),         # 6 channels: three bytes per pixel
     (8, 7, 3, 3, (1, 20, 22, 3)),       # 3-channel 8-bit input
     (3, 3, 2, 1, (2, 21, 17, 32)),      # 3-bit codes in 4-bit containers
+    (2, 3, 2, 1, (2, 13, 9, 64)),       # rows of 16 bytes at every width, windows of 3 and others
+    (2, 4, 3, 1, (1, 14, 11, 128)),
+    (4, 2, 2, 0, (2, 15, 12, 96)),
+    (4, 3, 1, 1, (1, 1, 1, 32)),        # one pixel: eight window positions outside
+    (8, 3, 1, 1, (2, 7, 5, 48)),
+    (8, 5, 2, 2, (1, 9, 10, 32)),
 ])
 def test_maxpool_parity(torch, bits, k, stride, pad, shape):
     dev = torch.device("cuda:0")
