@@ -585,7 +585,7 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
 
     // fp32 requantisation, where it is exact: codes of at most 4 bits, no skip or code
     // skips of side 0 (an offset per code). a and b per channel, for v = acc + bias
-    // (tables and lutf) and for the block-float accumulators (gf tables and glutf)
+    // (tables and lutf; the stem's for v = acc) and for the block-float accumulators (gf tables and glutf)
     std::vector<int32_t> lutf(lut.size()), glutf(lut.size());
     const int qmax = codes ? (1 << dc.bits_out) - 1 : 0;
     for (int l = 0; l < d.num_levels && codes && dc.bits_out <= 4 && d.skip_bits <= 4; ++l) {
@@ -608,7 +608,7 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
             const double bias = t[EPI_BIAS * h.cout_pad + c];
             ok = ok && K * ((1 << dc.bits_in) - 1) * wmax + std::fabs(bias) < (1 << 24);
             std::memcpy(&t[EPI_FA * h.cout_pad + c], &a, 4);
-            ok = ok && float_offset(a, lo, hi, 0, &t[EPI_FB * h.cout_pad + c]);
+            ok = ok && float_offset(a, lo, hi, stem ? bias : 0, &t[EPI_FB * h.cout_pad + c]);
             if (gok) {
                 const double gbias = gt[EPI_BIAS * gpad + c];
                 const float ga = a * unit;

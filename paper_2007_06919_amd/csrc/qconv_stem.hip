@@ -28,10 +28,12 @@
 // g holds channels 16g .. 16g+15 of a pixel (rows permuted at create), one 8-byte
 // store of 4-bit codes or four 16-byte stores of int32.
 //
-// Eight 800 x 1333 images: 110 us with windows built in LDS, 58 here (93 MB, 1.6
-// TB/s); with the weights in registers instead of LDS the fp32 epilogue spilled, 94.
-// What is left is instruction issue, the epilogue's five instructions a code above
-// all: the matrix cores need about 15 us, the memory 17.
+// Eight 800 x 1333 images: about 111 us with windows built in LDS, 58 here, 52 with the
+// next tile found by counting instead of three divisions, no masks for tiles inside the
+// image and the bias in the fp32 requantisation's b (93 MB, 1.8 TB/s); with the weights in
+// registers instead of LDS the fp32 epilogue spilled, 94. What is left is instruction
+// issue, the epilogue's five instructions a code above all: at the rates of an int8 MFMA
+// loop and of a copy the matrix cores need about 20 us and the memory 17.
 
 #include "epilogue.h"
 #include "internal.h"
@@ -94,20 +96,57 @@ __global__ void __launch_bounds__(256, OUTK == 0 && FAST == 1 ? 2 : 3) qconv_ste
         return t;
     };
 
+    // the tile after t (divisions are for the first one only)
+    auto advance = [&](Tile t) {
+        const MfmaSeg &S = A.seg[t.s];
+        t.ow += ST_TW;
+        if (t.ow >= S.wo) {
+            t.ow = 0;
+            t.oh += ST_TH;
+            if (t.oh >= S.ho) {
+                t.oh = 0;
+                if (++t.n == S.n) {
+                    t.n = 0;
+                    if (++t.ct == A.co_tiles) {
+                        t.ct = 0;
+                        ++t.s;
+                    }
+                }
+            }
+        }
+        return t;
+    };
+
     // ---- a thread's pieces of a tile: pixels 4c .. 4c + 3 of staged row y. info:
     // the shift to the first pixel's byte (bits 0-1) and which pixels lie in the image
     // (bits 4-7). Byte offsets in 32 bits: the image has fewer than 2^31 bytes,
     // checked on the host.
     dwords4 raw[ST_NP];
     int info[ST_NP];
+    bool inner = false;   // every staged pixel of the loaded tile lies in the image (and another row follows)
     auto load = [&](const Tile &t) {
         const MfmaSeg &S = A.seg[t.s];
         const int total = S.n * S.h * S.w * 3;       // image bytes (>= 3)
+        const int ih0 = 2 * t.oh - 3, iw0 = 2 * t.ow - 3;
+        inner = ih0 >= 0 && ih0 + ST_IR < S.h && iw0 >= 0 && iw0 + 4 * ST_CP <= S.w;
+        if (inner) {
+            const int base = ((t.n * S.h + ih0) * S.w + iw0) * 3;
+#pragma unroll
+            for (int k = 0; k < ST_NP; ++k) {
+                const int p = tid + 256 * k;
+                const int y = p / ST_CP, c = p - y * ST_CP;
+                const int b = base + y * (3 * S.w) + 12 * c;
+                info[k] = b & 3;
+                if (y < ST_IR)
+                    raw[k] = *(const dwords4 *)(S.x + (b & ~3));
+            }
+            return;
+        }
 #pragma unroll
         for (int k = 0; k < ST_NP; ++k) {
             const int p = tid + 256 * k;
             const int y = p / ST_CP, c = p - y * ST_CP;
-            const int ih = 2 * t.oh - 3 + y, iw = 2 * t.ow - 3 + 4 * c;
+            const int ih = ih0 + y, iw = iw0 + 4 * c;
             raw[k] = dwords4{0, 0, 0, 0};
             info[k] = 0;
             if (y >= ST_IR || (unsigned)ih >= (unsigned)S.h || iw >= S.w || iw < -3)
@@ -143,7 +182,7 @@ __global__ void __launch_bounds__(256, OUTK == 0 && FAST == 1 ? 2 : 3) qconv_ste
             v4i o;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int in = __builtin_amdgcn_sbfe(info[k], 4 + e, 1);
+                const int in = inner ? -1 : __builtin_amdgcn_sbfe(info[k], 4 + e, 1);
                 o[e] = (int)((px[e] & (uint32_t)in) ^ 0x80808080u);
             }
             *(v4i *)(lds + buf * ST_BUF + 16 * p) = o;   // rows are ST_CP pieces
@@ -173,7 +212,7 @@ __global__ void __launch_bounds__(256, OUTK == 0 && FAST == 1 ? 2 : 3) qconv_ste
     for (int t = t0; t < t1; ++t) {
         const MfmaSeg &S = A.seg[cur.s];
         const bool more = t + 1 < t1;
-        const Tile next = more ? locate(t + 1) : cur;
+        const Tile next = more ? advance(cur) : cur;
         if (more)
             load(next);
 
@@ -182,7 +221,9 @@ __global__ void __launch_bounds__(256, OUTK == 0 && FAST == 1 ? 2 : 3) qconv_ste
         v4i acc[MI][4];   // column tile 2 (output row) + (half of the tile's width)
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
-            const v4i bias = *(const v4i *)&tab[0][16 * g + 4 * i];
+            v4i bias = {0, 0, 0, 0};   // (fp32 requantisation: in b)
+            if constexpr (FAST != 2)
+                bias = *(const v4i *)&tab[0][16 * g + 4 * i];
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 acc[i][j] = bias;
