@@ -192,14 +192,15 @@ bool float_requant(int mult, int shift, int qmax, float *a, double *lo, double *
         t[m] = (double)((num + (uint64_t)mult - 1) / (uint64_t)mult);
     }
     for (int step = 0; step <= 4 && width < 8e-6; ++step)
-        for (int sign = -1; sign <= 1; sign += 2) {
+        for (int sign = -1; sign <= (step ? 1 : -1); sign += 2) {
             float c = a0;
             for (int k = 0; k < step; ++k)
                 c = std::nextafterf(c, sign > 0 ? 2 * a0 : 0.f);
             double l = -1e30, u = 1e30;
             for (int m = 1; m <= qmax; ++m) {
-                l = std::fmax(l, m - t[m] * c);
-                u = std::fmin(u, m - std::ldexp((double)m, -23) - (t[m] - 1) * c);
+                const double at = m - t[m] * c, below = m - m * 0x1p-23 - (t[m] - 1) * c;
+                l = at > l ? at : l;
+                u = below < u ? below : u;
             }
             if (u - l > width) {
                 width = u - l;
