@@ -300,7 +300,7 @@ __global__ void __launch_bounds__(64 * KW, 2) qconv_gf_kernel(MfmaArgs A)
 
     // ---------------------------------------------------------------- epilogue
     // fin[IG * jj + q]: row tile i0 + iw + q, pixel column jw + jj of the tile
-    constexpr float UNIT = F6 ? 64.f : F4 ? 2.f : 1.f;     // accumulator units per integer
+    constexpr float UNIT = F6 ? 64.f : 2.f;                // float kinds: accumulator units per integer
     if constexpr (KW == 1)
         wait_vmcnt<0>();                                   // the tables' copy
     const int cl = 16 * g + 4 * (i0 + iw);                 // first of the lane's 4 * IG channels, in the group
@@ -315,7 +315,10 @@ __global__ void __launch_bounds__(64 * KW, 2) qconv_gf_kernel(MfmaArgs A)
         for (int jj = 0; jj < JU; ++jj)
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                v[jj][e] = (int)(I8 ? fin[IG * jj + q][e] : fin[IG * jj + q][e] * UNIT) + bias[e];
+                if constexpr (I8)   // (int32 all the way: 8-bit sums go past 2^24)
+                    v[jj][e] = fin[IG * jj + q][e] + bias[e];
+                else
+                    v[jj][e] = (int)(fin[IG * jj + q][e] * UNIT) + bias[e];
         if constexpr (EP == 0) {
 #pragma unroll
             for (int jj = 0; jj < JU; ++jj) {

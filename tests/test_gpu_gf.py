@@ -135,3 +135,40 @@ def test_sums_at_the_exact_bound(torch, bits, cin, k):
     case.w_fields[:] = q
     case.w_fields[32:][rng.random(case.w_fields[32:].shape) < 0.05] = 0
     assert_same(gpu_conv(case, torch)[0], oracle_conv(case), f"{bits}-bit sums near 2^24")
+
+
+# 8-bit codes: (n, h, w, cin, cout, bits_out), the tiles and splits of the int8
+# form (32 x 32, 64 x 32 and 64 x 64 on 4 waves, 64 x 64 on 2 and on 1, 16
+# channels x 64 pixels for at most 4 channels)
+I8_SUMS = [(1, 9, 11, 256, 128, 32), (1, 9, 11, 144, 72, 8), (1, 25, 41, 256, 256, 32), (1, 50, 45, 256, 128, 32),
+           (1, 50, 45, 144, 256, 8), (1, 150, 201, 144, 8, 32), (1, 150, 201, 144, 8, 8), (1, 250, 270, 144, 8, 32),
+           (1, 13, 21, 144, 4, 32), (1, 13, 21, 144, 4, 8), (1, 13, 21, 256, 3, 32)]
+
+
+@pytest.mark.parametrize("case", I8_SUMS, ids=lambda c: "x".join(map(str, c)))
+def test_eight_bit_sums_past_the_fp32_integers(torch, case):
+    """Codes 255 and weights 127 or -127 but for a few 254s and 126s: the
+    re-centred sums are odd as well as even and beyond 2^24, where fp32 holds even
+    numbers only. Code outputs: a requantisation of scale 1 whose bias puts each
+    channel's interior sums within the code range, so that a sum off by one shows."""
+    n, h, w, cin, cout, bits_out = case
+    c = workloads.random_conv_case(seed=41, n=n, h=h, w=w, cin=cin, cout=cout, k=3, bits_in=8, bits_w=8,
+                                   bits_out=bits_out)
+    K = 9 * cin
+    rng = np.random.Generator(np.random.PCG64(K))
+    c.x[:] = np.where(rng.random(c.x.shape) < 1 / K, 254, 255)
+    wv = np.where(rng.random(c.w_fields.shape) < 0.01, 126, 127) * np.where(np.arange(cout) % 2, -1, 1).reshape(-1, 1, 1, 1)
+    c.w_fields[:] = wv & 0xFF
+    sums = wv.reshape(cout, -1).sum(1)
+    lv = c.levels[0]
+    if bits_out == 8:   # interior sums are 255 * sum(w) less about one |w|
+        lv["bias"] = (-255 * sums + np.where(sums > 0, 255, 0)).astype(np.int32)
+        lv["mult"][:], lv["shift"][:] = 1 << 30, -1
+    want = oracle_conv(c)
+    if bits_out == 32:
+        recentred = want.astype(np.int64) - lv["bias"] - 128 * sums
+        lost = recentred != recentred.astype(np.float32).astype(np.int64)
+        assert lost.mean() > 0.2, "the sums do not pass what fp32 holds"
+    else:
+        assert ((want > 0) & (want < 255)).mean() > 0.2
+    assert_same(gpu_conv(c, torch)[0], want, f"8-bit sums past 2^24 {case}")
