@@ -357,10 +357,11 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     if (K * ((1 << dc.bits_in) - 1) * wmax >= (1LL << 31))
         return fail(AQD_ERR_UNSUPPORTED, "accumulator could exceed int32 for this K and bitwidths");
 
-    // decode weight fields
+    // decode weight fields: value[] for everything a stored field can hold (a 3-bit
+    // weight is the low three bits of its container, whatever the fourth is)
     int16_t value[256];
-    for (int f = 0; f < (1 << dc.bits_w); ++f)
-        value[f] = (int16_t)weight_value(f, dc.bits_w, d.wenc);
+    for (int f = 0; f < (1 << d.bits_w); ++f)
+        value[f] = (int16_t)weight_value(f & ((1 << dc.bits_w) - 1), dc.bits_w, d.wenc);
     const int per = 8 / d.bits_w;
     const int wrow = d.cin * d.bits_w / 8;
     const int taps = d.kh * d.kw;
@@ -371,7 +372,7 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
             int16_t *dst = wv.data() + ((size_t)co * taps + t) * d.cin;
             for (int b = 0; b < wrow; ++b)
                 for (int e = 0; e < per; ++e)
-                    dst[b * per + e] = value[(row[b] >> (e * d.bits_w)) & ((1 << dc.bits_w) - 1)];
+                    dst[b * per + e] = value[(row[b] >> (e * d.bits_w)) & ((1 << d.bits_w) - 1)];
         }
 
     // MFMA kernel: 2/4-bit activations, weights that fit int8, 64-channel K

@@ -6,16 +6,18 @@ from oracle import ref
 from paper_2007_06919_amd import aqd, workloads
 
 
-def gpu_conv(case, torch, stream=None, split=False):
+def gpu_conv(case, torch, stream=None, split=False, w_packed=None):
     """Run a ConvCase through qconv_create/qconv_run (split: through
-    qconv_run_group_ws with the queried workspace, filled with junk first);
+    qconv_run_group_ws with the queried workspace, filled with junk first;
+    w_packed: the packed weights, where they are not simply the case's fields);
     returns the output bytes of every level."""
     dev = torch.device("cuda:0")
     skip_bits = case.skip_bits
     out_mode = aqd.OUT_INT32 if case.bits_out == 32 else aqd.OUT_CODES
     h = aqd.qconv_create(case.cin, case.cout, case.k, case.stride, case.pad, case.bits_in,
-                         case.bits_w, aqd.pack_codes(case.w_fields, case.bits_w), case.levels,
-                         wenc=case.wenc, out_mode=out_mode,
+                         case.bits_w,
+                         aqd.pack_codes(case.w_fields, case.bits_w) if w_packed is None else w_packed,
+                         case.levels, wenc=case.wenc, out_mode=out_mode,
                          bits_out=0 if case.bits_out == 32 else case.bits_out,
                          skip_bits=skip_bits, skip_up2=case.skip_up2)
     try:

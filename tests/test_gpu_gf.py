@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 
 from gpu_helpers import assert_same, check_case, gpu_conv, oracle_conv
-from paper_2007_06919_amd import workloads
+from paper_2007_06919_amd import aqd, workloads
 
 pytestmark = pytest.mark.gpu
 
@@ -172,3 +172,20 @@ def test_eight_bit_sums_past_the_fp32_integers(torch, case):
     else:
         assert ((want > 0) & (want < 255)).mean() > 0.2
     assert_same(gpu_conv(c, torch)[0], want, f"8-bit sums past 2^24 {case}")
+
+
+@pytest.mark.parametrize("wenc", [workloads.WENC_TWOS, workloads.WENC_PAPER_ODD])
+@pytest.mark.parametrize("shape", [(1, 9, 11, 64, 64, 3), (3, 61, 77, 64, 64, 3), (1, 67, 75, 1024, 512, 1)],
+                         ids=["gf", "fx3", "fx"])
+def test_three_bit_weights_with_the_spare_bit_set(torch, shape, wenc):
+    """A 3-bit weight field is the low three bits of its 4-bit container: the
+    fourth may hold anything, such as a copy of the sign."""
+    n, h, w, cin, cout, k = shape
+    case = workloads.random_conv_case(seed=83, n=n, h=h, w=w, cin=cin, cout=cout, k=k, bits_in=3, bits_w=3, bits_out=3,
+                                      wenc=wenc)
+    packed = aqd.pack_codes(case.w_fields, 3)
+    spare = np.random.Generator(np.random.PCG64(84)).integers(0, 256, size=packed.shape, dtype=np.uint8) & 0x88
+    if wenc == workloads.WENC_TWOS:
+        spare = (packed & 0x44) << 1   # sign extended
+    assert spare.any()
+    assert_same(gpu_conv(case, torch, w_packed=packed | spare)[0], oracle_conv(case), "3-bit weights, spare bit set")
