@@ -1143,22 +1143,8 @@ hipError_t launch_qconv_short(const MfmaArgs &a, hipStream_t stream)
     constexpr int BI = 4, MI = 8, NJ = 2, WC = 2, WP = 2, OCC = 3;
     if (a.bits_out != BI || (a.skip_bits != 0 && a.skip_bits != BI))
         return hipErrorInvalidValue;
-    dim3 grid(8 * a.tiles_per_xcd), block(64 * WC * WP);
-    bool fast = true;
-    for (int i = 0; i < a.nseg; ++i)
-        fast = fast && a.seg[i].fast;
-    if (a.skip_bits == 0) {
-        if (fast)
-            hipLaunchKernelGGL((qconv_mfma_kernel<BI, MI, NJ, WC, WP, 0, 0, 1, 0, OCC>), grid, block, 0, stream, a);
-        else
-            hipLaunchKernelGGL((qconv_mfma_kernel<BI, MI, NJ, WC, WP, 0, 0, 0, 0, OCC>), grid, block, 0, stream, a);
-    } else {
-        if (fast)
-            hipLaunchKernelGGL((qconv_mfma_kernel<BI, MI, NJ, WC, WP, 0, 1, 1, 0, OCC>), grid, block, 0, stream, a);
-        else
-            hipLaunchKernelGGL((qconv_mfma_kernel<BI, MI, NJ, WC, WP, 0, 1, 0, 0, OCC>), grid, block, 0, stream, a);
-    }
-    return hipGetLastError();
+    return a.skip_bits == 0 ? launch_t<BI, MI, NJ, WC, WP, 0, 0, OCC>(a, stream)
+                            : launch_t<BI, MI, NJ, WC, WP, 0, 1, OCC>(a, stream);
 }
 
 // streaming 256 x 64 tiles: two persistent workgroups per CU (a multiple of
