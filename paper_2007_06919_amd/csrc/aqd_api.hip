@@ -1046,7 +1046,15 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
 //    720 int32 P 133600 235 -> 164; 512 -> 512 P 8400 39.7 -> 24.7. At 256 channels in and
 //    up to 64 out gf stays up to t64 1100 (256 -> 36 P 66800: 23.1, fx3 26.1). 256 x 128
 //    tiles where the tiles still fill the chip (P 16700: 14.3, 256 x 64 15.5; 256 -> 720 P
-//    4200: 17.4, 13.0), at 2 bits 128 x 128 up to larger sizes (P 133600: 44.2, 42.0);
+//    4200: 17.4, 13.0), at 2 bits 128 x 128 up to larger sizes (P 133600: 44.2, 42.0). Not
+//    for more than 256 channels in and up to 128 out, where its 256 x 64 tiles are half
+//    or more padding (3x3 512 -> 64 t64 8775: fx3 403 us, own 226; 512 -> 128 t64 13000:
+//    fx3 261, fx 128 x 128 169, own 223), nor where the rows and columns of padding,
+//    which fx3 computes like any pixel, make it slower than what follows: at (h + 1)
+//    (w + 1) / (h w) = 1 it takes 0.60 of own's time at 256 -> 256 and t64 5000 (fx 0.75),
+//    0.70 at 512 -> 512 and t64 2000 (fx 0.73), 0.86 at 256 -> 64 and 3000 (own 1), 0.5
+//    at 128 -> 128 (own 1) and 0.33 at 64 -> 64 and 512 (gf 0.50); 512 -> 64 on images of
+//    2 x 1 took 5.5 times own's;
 //  * else t64 <= 512 (two tiles per CU): gf. 3x3 256 -> 256 P 4200 27.6 -> 11.3; 1x1 2048
 //    -> 512 P 1050 21 -> 7.4; 3x3 stride 2 2048 -> 256 P 273 30 -> 21, P 2184 37 -> 29;
 //    3x3 64 -> 64 P 1024 14.9 -> 4.6. So do the shapes of the direct kernel, at any
@@ -1056,7 +1064,10 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
 //    15.7), 3x3 128 -> 128 P 33400 18.3 -> 13.3, 3x3 256 -> 36 P 66800 35.7 -> 22.9;
 //    above, fx 128 x 128 for 65 to 128 channels and 9 steps or more, int32 at any
 //    size (3x3 256 -> 80 P 133600 54.9 -> 47.4), codes up to t64 1500 (3x3 128 -> 128
-//    stride 2 P 33400 18.9 -> 13.4, P 66800 19.6 -> 21.1);
+//    stride 2 P 33400 18.9 -> 13.4, P 66800 19.6 -> 21.1). 36 steps or more: fx 128 x 128
+//    for 65 to 128 channels at any size and of either width (3x3 512 -> 128 at t64 800:
+//    0.42 of own, gf 0.66; P 416000 224 -> 169), gf for up to 64 channels to t64 2000 (512
+//    -> 64 t64 1500: 0.85 of own, 2500: 1.08), at 2 bits at any size;
 //  * 256-channel tiles of 4 bits, 9 steps or more: fx 256 x 128, 256 x 64 while that
 //    leaves the chip short of tiles. 3x3 256 -> 256 P 133600 73.9 -> 57.9, P 16700
 //    23.9 -> 16.5; 3x3 512 -> 512 P 8400 39.9 -> 25.0, P 4200 22.6 -> 17.4; 3x3 256 ->
@@ -1076,9 +1087,11 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
         return false;
     const int steps = h0.gf_steps, cout = h0.d.cout;
     const bool f4 = h0.gf_kind == GF_F4, codes = h0.d.out_mode == AQD_OUT_CODES, mfma = own >= 0;
-    long long t64 = 0;
+    long long t64 = 0, pixels = 0, vpixels = 0;   // vpixels: with fx3's rows and columns of padding
     for (int i = 0; i < count; ++i) {
         const long long P = (long long)segs[i].n * chk[i].ho * chk[i].wo;
+        pixels += P;
+        vpixels += (long long)segs[i].n * (segs[i].h + 1) * (segs[i].w + 1);
         if (segs[i].conv->gf_kind != h0.gf_kind || chk[i].xbytes >= (1ull << 31) || P + 256 >= (1LL << 31))
             return false;   // (32-bit buffer offsets and pixel numbers)
         t64 += (P + 63) / 64 * h0.gf_groups;
@@ -1092,9 +1105,17 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
                               : cout % 4 == 0);
     const bool skip = h0.d.skip_bits != 0;
     const int cin = h0.d.cin;
+    // most that fx3's pixels with padding may be, in percent of the pixels
+    const bool plain = codes && !skip;
+    const int pad_limit = cin > 256 || (cin == 256 && cout <= 64)                           ? 120
+                          : cin <= 128 && (cin == 64 || cout <= 128) && plain && t64 <= 2000 ? 160
+                          : cout <= 128                                                     ? (plain || t64 <= 2000 ? 150 : 120)
+                          : cin == 256                                                      ? 125
+                                                                                            : 133;
     bool gf = false;
     if (tiled && t64 > (cin >= 256 ? 512 : 200) && h0.d.kh == 3 && h0.d.kw == 3 && h0.d.stride == 1 && h0.d.pad == 1 &&
-        (cin == 64 || cin == 128 || cin % 256 == 0) && !(cin >= 256 && cout <= 64 && t64 <= 1100)) {
+        (cin == 64 || cin == 128 || cin % 256 == 0) && !(cin >= 256 && cout <= 64 && t64 <= 1100) &&
+        !(cin > 256 && cout <= 128) && 100 * vpixels <= pad_limit * pixels) {
         kw = -1;
         if (cin == 64)
             wc = 1;
@@ -1111,9 +1132,12 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
         }
     } else if (!mfma || t64 <= 512) {
         gf = true;
-    } else if (f4 && (h0.d.skip_bits == 32 || (cout <= 64 && (codes || t64 <= 1100)) || (cout <= 128 && t64 <= 1100))) {
+    } else if (tiled && cout > 64 && cout <= 128 && steps >= 36) {
+        wc = 2;
+    } else if (f4 && (h0.d.skip_bits == 32 || (cout <= 64 && (codes || steps >= 36 || t64 <= 1100)) ||
+                      (cout <= 128 && t64 <= 1100))) {
         gf = true;
-    } else if (h0.gf_kind == GF_F6 && narrow && steps > 2 && t64 <= 1100) {
+    } else if (h0.gf_kind == GF_F6 && narrow && steps > 2 && t64 <= (steps >= 36 ? 2000 : 1100)) {
         gf = true;
     } else if (tiled && f4 && cout > 64 && !(cin == 64 && h0.d.kh == 1 && t64 > 8000)) {
         wc = cout <= 128 ? 2 : 4;

@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 from gpu_helpers import assert_same, check_case, gpu_conv, oracle_conv
+from oracle import ref
 from paper_2007_06919_amd import aqd, workloads
 
 pytestmark = pytest.mark.gpu
@@ -71,7 +72,8 @@ TILED = {
     "f4_128x128": dict(n=2, h=131, w=141, cin=96, cout=112, k=3, bits_in=2, bits_w=2, bits_out=2, skip_bits=2),
     # 3x3 stride 1 with the tile's input in LDS: every block size (64, 128, 256
     # channels, two blocks), tiles that span rows, images and pads (rows shorter
-    # than a tile, 1-pixel images), partial channel tiles
+    # than a tile), partial channel tiles; images on either side of the share of
+    # padding up to which this kernel runs, and of more than 256 channels to few
     "fx3_cin64": dict(n=3, h=61, w=77, cin=64, cout=64, k=3, wenc=1),
     "fx3_cin64_skip_3bit": dict(n=3, h=61, w=77, cin=64, cout=80, k=3, bits_in=3, bits_w=3, bits_out=3, skip_bits=3),
     "fx3_cin64_int32": dict(n=40, h=23, w=15, cin=64, cout=36, k=3, bits_out=32, wenc=1),
@@ -86,6 +88,12 @@ TILED = {
     "fx3_cin512_skip": dict(n=3, h=25, w=27, cin=512, cout=528, k=3, skip_bits=4),
     "fx3_1x1_images": dict(n=3500, h=1, w=1, cin=256, cout=256, k=3, wenc=1),
     "fx3_2x300": dict(n=7, h=2, w=300, cin=128, cout=256, k=3, wenc=1),
+    "fx3_4x5_images": dict(n=700, h=4, w=5, cin=128, cout=128, k=3, wenc=1),
+    "fx3_8x9_images_skip": dict(n=130, h=8, w=9, cin=256, cout=256, k=3, wenc=1, skip_bits=4),
+    "too_much_padding_3x4_images": dict(n=900, h=3, w=4, cin=64, cout=64, k=3, wenc=1),
+    "too_much_padding_7x8_images": dict(n=170, h=7, w=8, cin=256, cout=256, k=3, wenc=1),
+    "f6_128x128_cin512": dict(n=5, h=61, w=77, cin=512, cout=112, k=3, wenc=1, skip_bits=4),
+    "f4_128x128_cin512": dict(n=5, h=61, w=77, cin=512, cout=128, k=3, bits_in=2, bits_w=2, bits_out=2, wenc=1),
     "fx3_f4_cin64": dict(n=3, h=61, w=77, cin=64, cout=64, k=3, bits_in=2, bits_w=2, bits_out=2, wenc=1, skip_bits=2),
     "fx3_f4_cin128": dict(n=17, h=23, w=19, cin=128, cout=128, k=3, bits_in=2, bits_w=2, bits_out=2),
     "fx3_f4_cin256": dict(n=3, h=61, w=77, cin=256, cout=272, k=3, bits_in=2, bits_w=2, bits_out=2, skip_bits=2),
@@ -189,3 +197,27 @@ def test_three_bit_weights_with_the_spare_bit_set(torch, shape, wenc):
         spare = (packed & 0x44) << 1   # sign extended
     assert spare.any()
     assert_same(gpu_conv(case, torch, w_packed=packed | spare)[0], oracle_conv(case), "3-bit weights, spare bit set")
+
+
+def test_grouped_levels_of_small_images(torch):
+    """One 3x3 launch over levels whose last images are narrower than the filter:
+    the padding rows and columns of neighbouring images fall into one tile."""
+    sizes = [(41, 47), (9, 11), (2, 3), (1, 1), (1, 5)]
+    case = workloads.random_conv_case(seed=93, n=1, h=8, w=8, cin=256, cout=256, k=3, wenc=1, num_levels=len(sizes))
+    handle = aqd.qconv_create(256, 256, 3, 1, 1, 4, 4, aqd.pack_codes(case.w_fields, 4), case.levels, wenc=1)
+    rng = np.random.Generator(np.random.PCG64(94))
+    try:
+        segs, want = [], []
+        for lv, (h, w) in enumerate(sizes):
+            x = rng.integers(0, 16, size=(6, h, w, 256))
+            y = torch.full((6, h, w, 128), 0xA5, dtype=torch.uint8, device="cuda:0")
+            segs.append((handle, lv, 6, h, w, torch.from_numpy(aqd.pack_codes(x, 4)).cuda(), None, 0, 0, y))
+            t = case.levels[lv]
+            want.append(ref.pack_codes(ref.qconv(x, case.w_fields, 4, 1, 1, t["bias"], wenc=1, mult=t["mult"],
+                                                 shift=t["shift"], bits_out=4), 4))
+        aqd.qconv_run_group(segs)
+        torch.cuda.synchronize()
+        for s, w in zip(segs, want):
+            assert_same(s[-1].cpu().numpy(), w, f"level of {s[3]} x {s[4]}")
+    finally:
+        aqd.qconv_destroy(handle)
