@@ -1058,7 +1058,11 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
 //  * else t64 <= 512 (two tiles per CU): gf. 3x3 256 -> 256 P 4200 27.6 -> 11.3; 1x1 2048
 //    -> 512 P 1050 21 -> 7.4; 3x3 stride 2 2048 -> 256 P 273 30 -> 21, P 2184 37 -> 29;
 //    3x3 64 -> 64 P 1024 14.9 -> 4.6. So do the shapes of the direct kernel, at any
-//    size (3x3 256 -> 1 P 44600 1470 -> 8);
+//    size (3x3 256 -> 1 P 44600 1470 -> 8). Code outputs of 1x1 layers of 4 bits and up
+//    to 256 channels on the persistent tiles: gf over own 1.25 for 64 -> 64, 1.15 for 128
+//    -> 64, 0.95 for 128 -> 256, 0.84 for 256 -> 256 and 0.77 with a skip up to t64 100;
+//    1.6, 1.5, 1.23, 1.05 and 0.97 up to 256; 1.66, 1.57, 1.3, 1.2 and 1.16 above, 4 to 7
+//    us each. The 256 x 64 tiles of one step (128 -> 320) 0.81, 1.06 and 1.12;
 //  * 64- and 128-channel layers of 4 bits up to t64 1100, K beyond the streaming
 //    kernels' two steps: gf. 3x3 64 -> 64 P 66800 15.3 -> 10.0 (t64 2088: 14.8 ->
 //    15.7), 3x3 128 -> 128 P 33400 18.3 -> 13.3, 3x3 256 -> 36 P 66800 35.7 -> 22.9;
@@ -1112,6 +1116,14 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
                           : cout <= 128                                                     ? (plain || t64 <= 2000 ? 150 : 120)
                           : cin == 256                                                      ? 125
                                                                                             : 133;
+    // 1x1 layers of up to 256 channels on persistent tiles: gf only while its tiles are few
+    const bool stream = own == TILE_STREAM || own == TILE_STREAM_H128 || own == TILE_STREAM_C128 ||
+                        own == TILE_STREAM_C64 || own == TILE_WVS;
+    int gf_limit = 512;
+    if (stream)
+        gf_limit = cin == 64 || (cin == 128 && cout <= 128) ? 0 : cin == 256 && skip ? 256 : 100;
+    else if (own == TILE_256x64S && steps == 1)
+        gf_limit = 100;
     bool gf = false;
     if (tiled && t64 > (cin >= 256 ? 512 : 200) && h0.d.kh == 3 && h0.d.kw == 3 && h0.d.stride == 1 && h0.d.pad == 1 &&
         (cin == 64 || cin == 128 || cin % 256 == 0) && !(cin >= 256 && cout <= 64 && t64 <= 1100) &&
@@ -1130,7 +1142,7 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
             wc = skip && t64 <= 1500 ? 2 : 4;
             nj = !skip && t64 > 1000 ? 8 : 4;
         }
-    } else if (!mfma || t64 <= 512) {
+    } else if (!mfma || t64 <= gf_limit) {
         gf = true;
     } else if (tiled && cout > 64 && cout <= 128 && steps >= 36) {
         wc = 2;
