@@ -1078,12 +1078,18 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
 //    720 int32 P 133600 225 -> 175; 1x1 2048 -> 512 P 8400 20.8 -> 15.2. 8 steps: fx
 //    up to t64 1100 (1x1 1024 -> 256 P 16800 12.6 -> 10.4, P 33600 13.9 -> 15.1).
 //    One-round launches of the 256 x 144 tiles stay (P 33600 22.5 -> 23.6);
-//  * 2 bits (half the int8 kernels' time or less everywhere but in 1x1 layers of 64
-//    channels on many pixels, 81 -> 91, and 64-channel int32 layers): gf up to 64
-//    channels (3x3 64 -> 64 P 534400 37.4 -> 32.3), up to t64 1100 for 65 to 128, and
+//  * 2 bits (half the int8 kernels' time or less everywhere but in 1x1 layers of few
+//    channels on many pixels and 64-channel int32 layers): gf up to 64 channels (3x3 64 ->
+//    64 P 534400 37.4 -> 32.3), 1x1 layers of up to 256 channels in, 512 with a skip, only
+//    to t64 1100, 2000 from 192 channels in on (gf over own for 64 -> 64 1.02 at 800, 1.11
+//    at 1100, 1.6 at 3000; 256 -> 64 0.76, 0.9, 1.26), up to t64 1100 for 65 to 128, and
 //    for int32 skips (1x1 256 -> 1024 P 33600 75.9 -> 56.3); else fx: 3x3 128 -> 128 P
 //    133600 35.2 -> 20.7 (128 x 128), 3x3 256 -> 256 P 267200 96 -> 79.5 (256 x 128),
-//    P 33600 21.8 -> 16.2 (256 x 64), 1x1 512 -> 128 P 133600 24.2 -> 14.9.
+//    P 33600 21.8 -> 16.2 (256 x 64), 1x1 512 -> 128 P 133600 24.2 -> 14.9; 1x1 layers
+//    with a skip on 128 x 128 from t64 2000 on (over own, 256 x 64 and 128 x 128: 512 -> 512
+//    0.89, 0.81; 256 -> 256 t64 4000 0.96, 0.85), from 1100 on where 256-channel tiles would
+//    be a quarter or more padding (512 -> 320 0.79, 0.65), and then int32 outputs from 1500 on
+//    (128 -> 320 1.03, 0.94; t64 3000 1.08, 0.87).
 bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, MfmaArgs *out, GfPlan *plan)
 {
     const qconv_s &h0 = *segs[0].conv;
@@ -1110,7 +1116,8 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
     const bool skip = h0.d.skip_bits != 0;
     const int cin = h0.d.cin;
     // most that fx3's pixels with padding may be, in percent of the pixels
-    const bool plain = codes && !skip;
+    const bool plain = codes && !skip, one = h0.d.kh == 1 && h0.d.kw == 1;
+    const bool few = one && cin <= (skip ? 512 : 256);   // (2 bits) so few K steps that own is faster on many pixels
     const int pad_limit = cin > 256 || (cin == 256 && cout <= 64)                           ? 120
                           : cin <= 128 && (cin == 64 || cout <= 128) && plain && t64 <= 2000 ? 160
                           : cout <= 128                                                     ? (plain || t64 <= 2000 ? 150 : 120)
@@ -1146,13 +1153,16 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
         gf = true;
     } else if (tiled && cout > 64 && cout <= 128 && steps >= 36) {
         wc = 2;
-    } else if (f4 && (h0.d.skip_bits == 32 || (cout <= 64 && (codes || steps >= 36 || t64 <= 1100)) ||
+    } else if (f4 && (h0.d.skip_bits == 32 ||
+                      (cout <= 64 && (codes ? !few || t64 <= (cin <= 128 ? 1100 : 2000) : steps >= 36 || t64 <= 1100)) ||
                       (cout <= 128 && t64 <= 1100))) {
         gf = true;
     } else if (h0.gf_kind == GF_F6 && narrow && steps > 2 && t64 <= (steps >= 36 ? 2000 : 1100)) {
         gf = true;
-    } else if (tiled && f4 && cout > 64 && !(cin == 64 && h0.d.kh == 1 && t64 > 8000)) {
-        wc = cout <= 128 ? 2 : 4;
+    } else if (tiled && f4 && cout > 64 && !(cin == 64 && one && t64 > 8000)) {
+        const int g = h0.gf_groups;
+        const bool padded = (g + 3) / 4 * 2 > (g + 1) / 2;   // more tiles' worth of channels by fours than by twos
+        wc = cout <= 128 || (one && skip && t64 > (padded ? 1100 : 2000)) || (one && !codes && padded && t64 > 1500) ? 2 : 4;
         nj = wc == 4 && t64 > (codes ? 12000 : 4000) ? 8 : 4;
     } else if (tiled && !f4 && narrow && cout > 64 && steps >= 9 && (!codes || t64 <= 1500)) {
         wc = 2;

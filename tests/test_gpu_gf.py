@@ -70,6 +70,14 @@ TILED = {
                                skip_up2=True),
     "f4_256x128_int32": dict(n=1, h=201, w=203, cin=96, cout=516, k=3, bits_in=2, bits_w=2, bits_out=32, wenc=1),
     "f4_128x128": dict(n=2, h=131, w=141, cin=96, cout=112, k=3, bits_in=2, bits_w=2, bits_out=2, skip_bits=2),
+    # 1x1 layers of 2 bits: 128 x 128 tiles with partial ones at the end of the
+    # channels (320 = 2 1/2 tiles), skips and int32 outputs on many pixels; own tiles
+    # for 64 channels on many pixels
+    "f4_128x128_320": dict(n=1, h=131, w=141, cin=128, cout=320, k=1, bits_in=2, bits_w=2, bits_out=2, wenc=1),
+    "f4_128x128_320_skip": dict(n=1, h=131, w=141, cin=192, cout=320, k=1, bits_in=2, bits_w=2, bits_out=2, skip_bits=2,
+                                skip_up2=True),
+    "f4_128x128_256_int32": dict(n=1, h=183, w=191, cin=64, cout=260, k=1, bits_in=2, bits_w=2, bits_out=32, wenc=1),
+    "f4_own_64": dict(n=1, h=263, w=271, cin=64, cout=64, k=1, bits_in=2, bits_w=2, bits_out=2, skip_bits=2),
     # 3x3 stride 1 with the tile's input in LDS: every block size (64, 128, 256
     # channels, two blocks), tiles that span rows, images and pads (rows shorter
     # than a tile), partial channel tiles; images on either side of the share of
