@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -268,7 +269,7 @@ struct qconv_s {
     int tile_cfg, blk_co, blk_px;
     int co_tiles, ksteps, cout_pad;
     void *w_dev;       // the one allocation: weights, then the parts below
-    int32_t *epi_dev;  // [num_levels][EPI_FIELDS][cout_pad]
+    int32_t *epi_dev;  // [num_levels][EPI_FIELDS][cout_pad], and again for fp32 requantisation if a level has it
     int32_t *lut_dev;  // code skips: [num_levels][cout_pad][2^skip_bits] RSM(k, c, d), else null
     int32_t *lutf_dev, *gf_lutf;  // the same shape: fp32 b per code
     // per level: 1 = every shift >= 2, 2 = fp32 requantisation too; gf_fast: for the
@@ -517,6 +518,8 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
                 const int sh = e.shift[c];
                 t[EPI_MULT * h.cout_pad + c] = e.mult[c];
                 t[EPI_SHIFT * h.cout_pad + c] = sh;
+                t[EPI_SHR * h.cout_pad + c] = sh - 1;
+                t[EPI_RND * h.cout_pad + c] = sh >= 2 ? 1 << (sh - 2) : 0;
             }
             if (d.skip_bits) {
                 t[EPI_SKIP_C * h.cout_pad + c] = e.skip_c[c];
@@ -589,12 +592,13 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     // skips of side 0 (an offset per code). a and b per channel, for v = acc + bias
     // (tables and lutf; the stem's for v = acc) and for the block-float accumulators (gf tables and glutf)
     std::vector<int32_t> lutf(lut.size()), glutf(lut.size());
+    std::vector<int32_t> epif(epi);   // the same tables with a and b
     const int qmax = codes ? (1 << dc.bits_out) - 1 : 0;
     for (int l = 0; l < d.num_levels && codes && dc.bits_out <= 4 && d.skip_bits <= 4; ++l) {
         if (!h.fast[l] || (d.skip_bits && !h.side0[l]))
             continue;
         const qconv_epilogue_t &e = levels[l];
-        int32_t *t = epi.data() + (size_t)l * EPI_FIELDS * h.cout_pad;
+        int32_t *t = epif.data() + (size_t)l * EPI_FIELDS * h.cout_pad;
         const int gpad = 64 * h.gf_groups;
         int32_t *gt = gfe.data() + (size_t)l * EPI_FIELDS * gpad;
         const float unit = h.gf_kind == GF_F6 ? 64.f : h.gf_kind == GF_F4 ? 2.f : 1.f;
@@ -635,6 +639,8 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     for (int l = 0; l < d.num_levels; ++l)
         if (!h.gf_fast[l])
             h.gf_fast[l] = h.fast[l] ? 1 : 0;
+    if (std::count(h.fast.begin(), h.fast.end(), 2))
+        epi.insert(epi.end(), epif.begin(), epif.end());
 
     const char *inject = std::getenv("AQD_FAULT_INJECT");
     if (inject && std::strcmp(inject, "alloc") == 0)
@@ -1005,9 +1011,12 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
         if (segs[i].n == 0)
             continue;
         MfmaSeg &m = a.seg[k++];
-        if (!f32)
+        if (!f32) {
             m.fast = m.fast ? 1 : 0;
-        else if (h0.d.skip_bits)
+            continue;
+        }
+        m.epi += (size_t)segs[i].conv->d.num_levels * EPI_FIELDS * h0.cout_pad;
+        if (h0.d.skip_bits)
             m.lut = segs[i].conv->lutf_dev + segs[i].level * lut_words;
     }
     a.total_tiles = tiles;

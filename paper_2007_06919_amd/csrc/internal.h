@@ -56,7 +56,9 @@ void mfma_tile_shape(int tile_cfg, int *blk_co, int *blk_px, int *chan_per_lane)
 enum {
     EPI_BIAS = 0, EPI_MULT = 1, EPI_SHIFT = 2,            // v = acc + bias; requant M / 2^(31+shift)
     EPI_SKIP_C = 3, EPI_SKIP_D = 4, EPI_SKIP_SIDE = 5,    // Eq. 7-8 alignment
-    EPI_FA = 6, EPI_FB = 7,                               // fp32 requantisation: code = floor(v * a + b), clamped
+    // integer requantisation: shift - 1 and 2^(shift-2) (shift >= 2); in the tables of an
+    // fp32 one: code = floor(v * a + b), clamped
+    EPI_SHR = 6, EPI_RND = 7, EPI_FA = 6, EPI_FB = 7,
     EPI_FIELDS = 8
 };
 

@@ -525,13 +525,14 @@ __global__ void __launch_bounds__(64 * WC * WP, (Cfg<BI, MI, NJ, WC, WP, OCC>::W
             constexpr int i = decltype(ic)::value;
             const int cl = co_loc + 4 * i;
             const int4 m4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FB : EPI_MULT) * C::BCO + cl);
-            const int4 s4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FA : EPI_SHIFT) * C::BCO + cl);
+            const int4 s4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FA : FAST ? EPI_SHR : EPI_SHIFT) * C::BCO + cl);
             const int mult[4] = {m4.x, m4.y, m4.z, m4.w};
-            const int shf[4] = {s4.x - (FAST == 1), s4.y - (FAST == 1), s4.z - (FAST == 1), s4.w - (FAST == 1)};
+            const int shf[4] = {s4.x, s4.y, s4.z, s4.w};
             long long rnd[4] = {0, 0, 0, 0};  // 2^(shift-2) in the high word
             if constexpr (FAST == 1) {
-            rnd[0] = requant_rnd(s4.x); rnd[1] = requant_rnd(s4.y);
-            rnd[2] = requant_rnd(s4.z); rnd[3] = requant_rnd(s4.w);
+                const int4 r4 = *(const int4 *)(prm + EPI_RND * C::BCO + cl);
+                rnd[0] = (long long)r4.x << 32; rnd[1] = (long long)r4.y << 32;
+                rnd[2] = (long long)r4.z << 32; rnd[3] = (long long)r4.w << 32;
             }
             int sc[4] = {0, 0, 0, 0}, sd[4] = {0, 0, 0, 0}, sside[4] = {0, 0, 0, 0};
             long long srnd[4] = {0, 0, 0, 0};  // rounding terms of the alignment
@@ -974,13 +975,14 @@ __global__ void __launch_bounds__(256, 2) qconv_stream_kernel(MfmaArgs A)
                 constexpr int i = decltype(ic)::value;
                 const int cl = co_loc + 4 * i;
                 const int4 m4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FB : EPI_MULT) * BCO + cl);
-                const int4 s4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FA : EPI_SHIFT) * BCO + cl);
+                const int4 s4 = *(const int4 *)(prm + (FAST == 2 ? EPI_FA : FAST ? EPI_SHR : EPI_SHIFT) * BCO + cl);
                 const int mult[4] = {m4.x, m4.y, m4.z, m4.w};
-                const int shf[4] = {s4.x - (FAST == 1), s4.y - (FAST == 1), s4.z - (FAST == 1), s4.w - (FAST == 1)};
+                const int shf[4] = {s4.x, s4.y, s4.z, s4.w};
                 long long rnd[4] = {0, 0, 0, 0};
                 if constexpr (FAST == 1) {
-            rnd[0] = requant_rnd(s4.x); rnd[1] = requant_rnd(s4.y);
-            rnd[2] = requant_rnd(s4.z); rnd[3] = requant_rnd(s4.w);
+                    const int4 r4 = *(const int4 *)(prm + EPI_RND * BCO + cl);
+                    rnd[0] = (long long)r4.x << 32; rnd[1] = (long long)r4.y << 32;
+                    rnd[2] = (long long)r4.z << 32; rnd[3] = (long long)r4.w << 32;
                 }
                 int sc[4] = {0, 0, 0, 0}, sd[4] = {0, 0, 0, 0}, sside[4] = {0, 0, 0, 0};
                 long long srnd[4] = {0, 0, 0, 0};  // rounding terms of the alignment
