@@ -1079,7 +1079,8 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
 //    size (3x3 256 -> 80 P 133600 54.9 -> 47.4), codes up to t64 1500 (3x3 128 -> 128
 //    stride 2 P 33400 18.9 -> 13.4, P 66800 19.6 -> 21.1). 36 steps or more: fx 128 x 128
 //    for 65 to 128 channels at any size and of either width (3x3 512 -> 128 at t64 800:
-//    0.42 of own, gf 0.66; P 416000 224 -> 169), gf for up to 64 channels to t64 2000 (512
+//    0.42 of own, gf 0.66; P 416000 224 -> 169), 256-channel tiles for 129 to 255 of 4
+//    bits (512 -> 192 t64 600: 0.44, 128 x 128 0.51, gf 0.65), gf for up to 64 channels to t64 2000 (512
 //    -> 64 t64 1500: 0.85 of own, 2500: 1.08), at 2 bits at any size;
 //  * 256-channel tiles of 4 bits, 9 steps or more: fx 256 x 128, 256 x 64 while that
 //    leaves the chip short of tiles. 3x3 256 -> 256 P 133600 73.9 -> 57.9, P 16700
@@ -1095,7 +1096,7 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
 //    for int32 skips (1x1 256 -> 1024 P 33600 75.9 -> 56.3); else fx: 3x3 128 -> 128 P
 //    133600 35.2 -> 20.7 (128 x 128), 3x3 256 -> 256 P 267200 96 -> 79.5 (256 x 128),
 //    P 33600 21.8 -> 16.2 (256 x 64), 1x1 512 -> 128 P 133600 24.2 -> 14.9; 1x1 layers
-//    with a skip on 128 x 128 from t64 2000 on (over own, 256 x 64 and 128 x 128: 512 -> 512
+//    with a skip and up to 8 steps on 128 x 128 from t64 2000 on (over own, 256 x 64 and 128 x 128: 512 -> 512
 //    0.89, 0.81; 256 -> 256 t64 4000 0.96, 0.85), from 1100 on where 256-channel tiles would
 //    be a quarter or more padding (512 -> 320 0.79, 0.65), and then int32 outputs from 1500 on
 //    (128 -> 320 1.03, 0.94; t64 3000 1.08, 0.87).
@@ -1160,18 +1161,19 @@ bool plan_gf(int count, const qconv_seg_t *segs, const SegCheck *chk, int own, M
         }
     } else if (!mfma || t64 <= gf_limit) {
         gf = true;
-    } else if (tiled && cout > 64 && cout <= 128 && steps >= 36) {
-        wc = 2;
+    } else if (tiled && cout > 64 && steps >= 36 && (cout <= 128 || (!f4 && narrow))) {
+        wc = cout <= 128 ? 2 : 4;
+        nj = wc == 4 && t64 > 1024 && !skip ? 8 : 4;
     } else if (f4 && (h0.d.skip_bits == 32 ||
                       (cout <= 64 && (codes ? !few || t64 <= (cin <= 128 ? 1100 : 2000) : steps >= 36 || t64 <= 1100)) ||
                       (cout <= 128 && t64 <= 1100))) {
         gf = true;
-    } else if (h0.gf_kind == GF_F6 && narrow && steps > 2 && t64 <= (steps >= 36 ? 2000 : 1100)) {
+    } else if (h0.gf_kind == GF_F6 && narrow && steps > 2 && t64 <= (steps >= 36 && cout <= 64 ? 2000 : 1100)) {
         gf = true;
     } else if (tiled && f4 && cout > 64 && !(cin == 64 && one && t64 > 8000)) {
         const int g = h0.gf_groups;
         const bool padded = (g + 3) / 4 * 2 > (g + 1) / 2;   // more tiles' worth of channels by fours than by twos
-        wc = cout <= 128 || (one && skip && t64 > (padded ? 1100 : 2000)) || (one && !codes && padded && t64 > 1500) ? 2 : 4;
+        wc = cout <= 128 || (one && skip && (padded ? t64 > 1100 : t64 > 2000 && steps <= 8)) || (one && !codes && padded && t64 > 1500) ? 2 : 4;
         nj = wc == 4 && t64 > (codes ? 12000 : 4000) ? 8 : 4;
     } else if (tiled && !f4 && narrow && cout > 64 && steps >= 9 && (!codes || t64 <= 1500)) {
         wc = 2;

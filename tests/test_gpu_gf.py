@@ -101,6 +101,8 @@ TILED = {
     "too_much_padding_3x4_images": dict(n=900, h=3, w=4, cin=64, cout=64, k=3, wenc=1),
     "too_much_padding_7x8_images": dict(n=170, h=7, w=8, cin=256, cout=256, k=3, wenc=1),
     "f6_128x128_cin512": dict(n=5, h=61, w=77, cin=512, cout=112, k=3, wenc=1, skip_bits=4),
+    "f6_256x64_cin512_192": dict(n=4, h=3, w=1200, cin=512, cout=192, k=3, wenc=1, skip_bits=4),
+    "f6_256x128_cin512_144": dict(n=1, h=2, w=24000, cin=512, cout=144, k=3, bits_in=3, bits_w=2, bits_out=3),
     "f4_128x128_cin512": dict(n=5, h=61, w=77, cin=512, cout=128, k=3, bits_in=2, bits_w=2, bits_out=2, wenc=1),
     "fx3_f4_cin64": dict(n=3, h=61, w=77, cin=64, cout=64, k=3, bits_in=2, bits_w=2, bits_out=2, wenc=1, skip_bits=2),
     "fx3_f4_cin128": dict(n=17, h=23, w=19, cin=128, cout=128, k=3, bits_in=2, bits_w=2, bits_out=2),
