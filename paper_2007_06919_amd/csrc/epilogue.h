@@ -8,7 +8,7 @@
 // RSM(a, c, d) = floor((a*c + 2^(d-1)) / 2^d), and a*c for d = 0. With
 // |a| < 2^31 and |c| < 2^31 the product stays below 2^62 and the rounding
 // constant below 2^61, so the 64-bit sum cannot overflow; an arithmetic
-// right shift of a signed 64-bit value is the floor division.
+// right shift of a signed value is the floor division.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -16,37 +16,41 @@
 
 namespace aqd {
 
-// p >> d and 2^(d-1) (0 for d = 0), 0 <= d <= 62, in 32-bit shifts: the 64-bit
-// shift instructions give wrong results now and then where the register of the
-// shift amount is the last one allocated to the wave (v167 of 168 in one form of
-// the register-fed kernel, where just the channels shifted by it came out wrong),
-// and no source can say which register the compiler takes.
-__device__ __forceinline__ long long shift_right(long long p, int d)
-{
-    const int hi = (int)(p >> 32), h = hi >> (d & 31);
-    const unsigned l = __builtin_amdgcn_alignbit((unsigned)hi, (unsigned)p, (unsigned)d);
-    const bool wide = d & 32;
-    return (long long)((unsigned long long)(unsigned)(wide ? hi >> 31 : h) << 32 | (wide ? (unsigned)h : l));
-}
-__device__ __forceinline__ long long half_of(int d)
-{
-    const unsigned b = d > 0 ? 1u << ((d - 1) & 31) : 0u;
-    return (long long)(d > 32 ? (unsigned long long)b << 32 : b);
-}
+// The 64-bit shifts below are made of 32-bit ones: the 64-bit shift instructions
+// give wrong results now and then where the register of the shift amount is the
+// last one allocated to the wave (v167 of 168 in one form of the register-fed
+// kernel, where just the channels shifted by it came out wrong), and no source can
+// say which register the compiler takes.
 
-__device__ __forceinline__ long long rsm(long long a, long long c, int d) { return shift_right(a * c + half_of(d), d); }
+// RSM(a, c, d) for 0 <= d <= 31 (the alignment's exponents)
+__device__ __forceinline__ long long rsm(int a, int c, int d)
+{
+    const long long p = (long long)a * c + (long long)((1u << d) >> 1);
+    const int hi = (int)(p >> 32);
+    return (long long)((unsigned long long)(unsigned)(hi >> d) << 32 |
+                       __builtin_amdgcn_alignbit((unsigned)hi, (unsigned)p, (unsigned)d));
+}
 
 __device__ __forceinline__ long long align_add(int v, int k, int c, int d, int side)
 {
-    return side == 0 ? (long long)v + rsm(k, c, d) : rsm(v, c, d) + (long long)k;
+    return (long long)(side ? k : v) + rsm(side ? v : k, c, d);
 }
 
+// clamp(RSM(u, mult, d), 0, qmax), d = 31 + shift in 0 .. 62: with the high word h and
+// the low word l of the rounded product shifted by d modulo 32, the result is h from
+// d = 32 on; below, l while h is 0, else past the range on h's side (h == 0 ? l : h | 2^30
+// costs the register-fed kernels 50 spilled registers)
 __device__ __forceinline__ uint32_t requant_clamp(long long u, int mult, int shift, int qmax)
 {
-    long long y = rsm(u, mult, 31 + shift);
-    y = y < 0 ? 0 : y;
-    y = y > qmax ? qmax : y;
-    return (uint32_t)y;
+    const int d = 31 + shift;
+    const unsigned half = d > 0 ? 1u << ((d - 1) & 31) : 0u;   // of 2^(d-1)
+    const long long p = u * mult + (long long)(d > 32 ? (unsigned long long)half << 32 : half);
+    const int hi = (int)(p >> 32), h = hi >> (d & 31);
+    const unsigned l = __builtin_amdgcn_alignbit((unsigned)hi, (unsigned)p, (unsigned)d);
+    const int side = h < -1 ? -1 : h > 1 ? 1 : h;
+    const int below = side * (qmax + 1) + (int)(l < (unsigned)qmax ? l : (unsigned)qmax);
+    const int y = d & 32 ? h : below;
+    return (uint32_t)(y < 0 ? 0 : y > qmax ? qmax : y);
 }
 
 // Code of channel c of a packed row (bits in {2, 4, 8}).
