@@ -72,9 +72,9 @@ int tile_row_channel(int rho, int cpl)
     return w * slice + cpl * g + 4 * i + e;
 }
 
-// FP4 path (qconv_fp4.hip): position kappa of a 256-channel stage in LDS
-// holds channel fp4_channel(kappa). A copy lane spreads 32 packed 2-bit codes
-// (channels 32c .. 32c+31) into 16-byte column c: word 0 = the even channels
+// Block-float kernels, 2-bit codes: position kappa of a chunk of channels holds
+// channel fp4_channel(kappa). 32 packed 2-bit codes (channels 32c .. 32c+31) are
+// spread into 16 bytes: word 0 = the even channels
 // of the first 16, word 1 = their odd ones, words 2 and 3 the same for the
 // second 16; nibble n of a word is its n-th channel.
 int fp4_channel(int kappa)
@@ -396,7 +396,7 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
                              (codes ? (d.cout % 16 == 0 && d.bits_out == d.bits_in &&
                                        (d.skip_bits == 0 || d.skip_bits == d.bits_in || d.skip_bits == 32))
                                     : d.cout % 4 == 0));
-    // 2-bit codes and weights in 256-channel chunks: the scaled FP4 MFMA, exact
+    // 2-bit codes and weights in 256-channel chunks: block-float kernels only, exact
     // while every partial sum stays below 2^24 (K * 3 * max|w| < 2^24)
     const char *no_fp4 = std::getenv("AQD_NO_FP4");
     const bool fp4 = mfma && !(no_fp4 && std::strcmp(no_fp4, "1") == 0) && dc.bits_in == 2 && dc.bits_w == 2 &&
@@ -449,27 +449,7 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
                         }
             }
     } else if (fp4) {
-        // tiles [co_tile][128-channel K step][row rho][64 bytes]: channel
-        // tile_row_channel(rho) of the tile; nibble kappa (byte kappa / 2, low
-        // nibble first) = e2m1 of the weight of input channel
-        // fp4_channel(128 q + kappa) of the stage, q = K step % 2
-        const int k4pt = d.cin / 128, ks4 = taps * k4pt;
-        int order[256];
-        for (int kap = 0; kap < 256; ++kap)
-            order[kap] = fp4_channel(kap);
-        wbuf.assign((size_t)h.co_tiles * ks4 * 256 * 64, 0);
-        for (int ct = 0; ct < h.co_tiles; ++ct)
-            for (int ks = 0; ks < ks4; ++ks) {
-                const int tap = ks / k4pt, c128 = ks % k4pt;
-                const int stage0 = 256 * (c128 / 2), q = c128 % 2;
-                for (int rho = 0; rho < 256; ++rho) {
-                    const int co = ct * 256 + tile_row_channel(rho, cpl);
-                    uint8_t *dst = wbuf.data() + (((size_t)ct * ks4 + ks) * 256 + rho) * 64;
-                    const int16_t *src = wv.data() + ((size_t)co * taps + tap) * d.cin + stage0;
-                    for (int kap = 0; kap < 128; ++kap)
-                        dst[kap / 2] |= (uint8_t)(e2m1_nibble(src[order[128 * q + kap]]) << (4 * (kap % 2)));
-                }
-            }
+        // (every launch runs on the block-float kernels, with weights of their own)
     } else if (mfma) {
         // tiles [co_tile][k step][row rho][byte p]: channel tile_row_channel(rho) of the tile,
         // input channel widened_channel(p) of the K step's 64-channel chunk
@@ -657,7 +637,7 @@ aqd_status_t qconv_create(const qconv_desc_t *desc, const uint8_t *w_packed,
     // (64 KiB) of padding past the end, which the register-fed kernel's
     // look-ahead may read (never use)
     auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    const size_t o_epi = up(wbuf.size() + (mfma ? 4 * 256 * KC : 0)), o_lut = o_epi + up(epi.size() * sizeof(int32_t)),
+    const size_t o_epi = up(wbuf.size() + (mfma && !fp4 ? 4 * 256 * KC : 0)), o_lut = o_epi + up(epi.size() * sizeof(int32_t)),
                  o_lutf = o_lut + up(lut.size() * sizeof(int32_t)), o_glutf = o_lutf + up(lut.size() * sizeof(int32_t)),
                  o_gfw = o_glutf + up(lut.size() * sizeof(int32_t)), o_gfe = o_gfw + up(gfw.size()),
                  total = o_gfe + gfe.size() * sizeof(int32_t);
@@ -848,7 +828,9 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
         aqd_status_t st = check_seg(segs[i], &chk[i]);
         if (st != AQD_OK)
             return st;
-        REQUIRE(same_config(segs[0].conv->d, segs[i].conv->d) && segs[0].conv->qmax == segs[i].conv->qmax,
+        // (the tile differs where handles were created with and without AQD_NO_FP4)
+        REQUIRE(same_config(segs[0].conv->d, segs[i].conv->d) && segs[0].conv->qmax == segs[i].conv->qmax &&
+                    segs[0].conv->tile_cfg == segs[i].conv->tile_cfg,
                 "grouped handles must share shapes, bitwidths and modes");
     }
     for (int i = 0; i < count; ++i)
@@ -874,7 +856,7 @@ aqd_status_t prepare_group(int count, const qconv_seg_t *segs, SegCheck *chk, Mf
     // splitting K is the better cure) on 256 x 64 tiles two to a CU (measured:
     // from ~260 tiles on, the larger tile is faster)
     int tile_cfg = h0.tile_cfg, blk_px = h0.blk_px;
-    // the register-fed, FP4 and 8-bit kernels address each segment's input
+    // the register-fed, block-float and 8-bit kernels address each segment's input
     // with 32-bit buffer offsets
     bool x_small = true;
     for (int i = 0; i < count; ++i)
@@ -1279,8 +1261,8 @@ void plan_split(const MfmaArgs &a, int *nparts, int *kchunk)
     long long P = 0;
     for (int i = 0; i < a.nseg; ++i)
         P += a.seg[i].P;
-    // the FP4 path: half the MFMA time per 64-channel step, parts of whole
-    // 256-channel stages (4 steps)
+    // FP4 handles (their launches never split; the size that they ask for stays):
+    // half the MFMA time per 64-channel step, parts of whole 256-channel stages (4 steps)
     const bool fp4 = a.tile_cfg == TILE_FP4, b8 = a.tile_cfg == TILE_B8;
     const double step_scale = fp4 ? 0.5 : 1.0;
     const int align = fp4 ? 4 : b8 ? 2 : 1;

@@ -28,12 +28,12 @@ enum { TILE_256x128 = 0, TILE_128x256 = 1, TILE_64x512 = 2,
        // cin a multiple of 256, code outputs: 256 x 128 tiles with the weights
        // read into registers (qconv_wv.hip), same weight layout as 256x128
        TILE_WV = 11,
-       // 2-bit codes and 2-bit weights, cin and cout multiples of 256: 256 x 128
-       // tiles on the scaled FP4 MFMA (qconv_b16.hip), weights stored as e2m1
-       // nibbles at create (64 bytes per row and 128-channel K step)
+       // 2-bit codes and 2-bit weights, cin and cout multiples of 256: every launch
+       // runs on the block-float kernels; the tile stands for the handle's path and
+       // its split-K accounting (256 x 128 tiles, K in 256-channel stages)
        TILE_FP4 = 12,
        // 8-bit codes, cin a multiple of 128, int32 outputs: 256 x 128 tiles on
-       // the int8 MFMA (qconv_b16.hip), weights in channel order at create
+       // the int8 MFMA (qconv_b8.hip), weights in channel order at create
        TILE_B8 = 13,
        // the 7x7 stride-2 stem on a 3-channel 8-bit image: 64 channels x 8 rows
        // of 32 pixels, K = the whole window (qconv_stem.hip)
@@ -117,9 +117,9 @@ hipError_t launch_qconv_wv(const MfmaArgs &a, hipStream_t stream);
 // fused projection shortcut, both 1x1 with cin and cin2 multiples of 256, on
 // TILE_WV64's 256 x 64 tiles (qconv_wv.hip)
 hipError_t launch_qconv_wv_proj(const MfmaArgs &a, hipStream_t stream);
-// TILE_FP4 (code_bits 2) and TILE_B8 (code_bits 8) launches (qconv_b16.hip);
-// a.ksteps and a.kchunk in 64-channel steps, multiples of a stage (4 and 2)
-hipError_t launch_qconv_b16(int code_bits, const MfmaArgs &a, hipStream_t stream);
+// TILE_B8 launches (qconv_b8.hip); a.ksteps and a.kchunk in 64-channel steps, multiples
+// of a stage (2)
+hipError_t launch_qconv_b8(const MfmaArgs &a, hipStream_t stream);
 // Global-fed launches (qconv_gf.hip): operand kinds of the weights stored for
 // them at create ([64-channel group][K step][4 row tiles][WB bytes], WB =
 // GF_F6_TILE for e2m3, else 1024; per row tile the 16 bytes of each lane, then
@@ -170,7 +170,7 @@ struct DirectArgs {
     const void *skip;
     void *y;
     const int16_t *wt;   // [cout][kh][kw][cin] decoded values
-    const int32_t *epi;  // [6][cout]
+    const int32_t *epi;  // [EPI_FIELDS][cout]
     int n, h, w, ho, wo, hs, ws;
     int cin, cout, kh, kw, stride, pad;
     int bits_in, out_bits, skip_bits, up2;

@@ -23,11 +23,12 @@
 // Buffer loads return zeros past a buffer's size: padding taps, pixels past the
 // end and steps past the last cost no branch.
 //
-// What bounds it (3x3 256 -> 256 on 267200 pixels, 256 x 128 tiles: 140 us on the
-// int8 register-fed kernel, 107 us here, 2940 int TOPS of the 7000 the MFMA alone
-// reaches on these operands): timing variants that leave work out gain 9% without
-// the weight loads, 19% without the copies' widening and LDS writes, 19% without the
-// epilogue; matrix cores busy 32%, LDS 21%.
+// What bounds it (measured on 3x3 256 -> 256 stride 1, 267200 pixels, 256 x 128 tiles, a
+// layer that the 3x3 kernel below takes since: 140 us on the int8 register-fed kernel,
+// 107 us here, 2940 int TOPS of the 7000 the MFMA alone reaches on these operands):
+// timing variants that leave work out gain 9% without the weight loads, 19% without the
+// copies' widening and LDS writes, 19% without the epilogue; matrix cores busy 32%,
+// LDS 21%. What it runs now: other strides, 1x1 layers, padded images (plan_gf).
 //
 // Epilogue (Sec. 3.2.2-3.2.3, Eq. 6-8, Eq. 2 on integers): a lane holds 16
 // consecutive channels of NJ pixels.
@@ -859,9 +860,7 @@ hipError_t launch_kind(const MfmaArgs &a, const GfPlan &p, int fast, hipStream_t
                    : tile == 24 ? launch3_modes<KIND, 2, 4, 8, 0>(a, fast, stream)
                                 : hipErrorInvalidValue;
         if (a.cin == 128)
-            return tile == 48   ? launch3_modes<KIND, 4, 8, 4, 0>(a, fast, stream)
-                   : tile == 24 ? launch3_modes<KIND, 2, 4, 4, 0>(a, fast, stream)
-                                : hipErrorInvalidValue;
+            return tile == 24 ? launch3_modes<KIND, 2, 4, 4, 0>(a, fast, stream) : hipErrorInvalidValue;
         if (a.cin == 64)
             return tile == 14 ? launch3_modes<KIND, 1, 4, 2, 0>(a, fast, stream) : hipErrorInvalidValue;
         return tile == 44 ? launch3_modes<KIND, 4, 4, 8, 1>(a, fast, stream) : hipErrorInvalidValue;

@@ -9,7 +9,7 @@
 // What bounds such a launch is the length of its serial chain: a tile's K steps
 // run one after another on one wave's MFMAs at the latency of a copy, a barrier
 // and an LDS read each, with most of the chip idle. Here a tile is 64 x 64 or
-// smaller, its K range is cut between 2 to 8 waves, each wave keeps the loads of
+// smaller, its K range is cut between 1 to 4 waves, each wave keeps the loads of
 // three or four steps in flight, and the sums are combined inside the workgroup
 // (no second launch, no partial sums in memory). 3x3 256 -> 256 on 4200 pixels:
 // 27.6 -> 11.3 us, 3x3 64 -> 64 on 1024: 14.9 -> 4.6 us (more at the rule that

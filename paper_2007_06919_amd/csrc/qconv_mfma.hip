@@ -1265,8 +1265,8 @@ hipError_t launch_qconv_mfma(int bits_in, const MfmaArgs &a, hipStream_t stream)
         case TILE_128x256: return launch_modes<4, 4, 8, 2, 2>(a, stream);
         case TILE_64x512: return launch_modes<4, 4, 8, 1, 4>(a, stream);
         }
-    } else if ((bits_in == 2 && a.tile_cfg == TILE_FP4) || (bits_in == 8 && a.tile_cfg == TILE_B8)) {
-        return launch_qconv_b16(bits_in, a, stream);
+    } else if (bits_in == 8 && a.tile_cfg == TILE_B8) {
+        return launch_qconv_b8(a, stream);
     } else if (bits_in == 8 && a.tile_cfg == TILE_STEM) {
         return launch_qconv_stem(a, stream);
     } else if (bits_in == 2) {

@@ -1,9 +1,9 @@
 """Wait-state scan of AMDGPU assembly around MFMA instructions.
 
-The FP4 kernel issues its MFMAs as inline assembly (so that they accumulate
-in place), which the compiler does not recognise as MFMAs: it inserts none of
-the wait states the matrix-core dependency rules ask for. This scan checks the
-built code for them: no instruction may write an MFMA source register within
+The matrix-core dependency rules ask for wait states between an MFMA and what
+writes its sources or touches its result, and inline assembly next to one can undo
+the compiler's placement. This scan checks the built code for them: no instruction
+may write an MFMA source register within
 2 wait states before the MFMA, and no instruction other than a later MFMA
 accumulating into the same registers may touch an MFMA's destination within
 `after` wait states (the rules ask for at most 18 for the longest MFMAs; the
