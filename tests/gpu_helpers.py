@@ -6,9 +6,17 @@ from oracle import ref
 from paper_2007_06919_amd import aqd, workloads
 
 
+def weights_of(kind, bits_in, bits_w, wenc):
+    """(bits_w, wenc) of a parity case. "own": weights that no block-float kernel takes,
+    so that the launch runs on the kernel of the handle's own layout at any size
+    (8-bit weights on 3- and 4-bit codes, 4-bit weights on 2-bit codes)."""
+    return (bits_w, wenc) if kind == "narrow" else (4 if bits_in == 2 else 8, workloads.WENC_TWOS)
+
+
 def gpu_conv(case, torch, stream=None, split=False, w_packed=None):
     """Run a ConvCase through qconv_create/qconv_run (split: through
-    qconv_run_group_ws with the queried workspace, filled with junk first;
+    qconv_run_group_ws with the queried workspace, filled with junk first,
+    which the launch has to change for "parts" and to leave alone for "whole";
     w_packed: the packed weights, where they are not simply the case's fields);
     returns the output bytes of every level."""
     dev = torch.device("cuda:0")
@@ -46,6 +54,8 @@ def gpu_conv(case, torch, stream=None, split=False, w_packed=None):
             else:
                 aqd.qconv_run(h, level, case.n, case.h, case.w, x, skip, hs, ws, y, stream)
             torch.cuda.synchronize()
+            if split:
+                assert bool((wsbuf != 0x77).any()) == (split == "parts"), f"workspace: expected {split}"
             outs.append(y.cpu().numpy().copy())
         return outs
     finally:

@@ -10,7 +10,7 @@ take).
 import numpy as np
 import pytest
 
-from gpu_helpers import assert_same, check_case, gpu_conv, oracle_conv
+from gpu_helpers import assert_same, check_case, gpu_conv, oracle_conv, weights_of
 from oracle import ref
 from paper_2007_06919_amd import aqd, workloads
 
@@ -63,8 +63,12 @@ def test_conv_mfma_general_requant_path(torch):
 
 
 @pytest.mark.parametrize("case", MFMA_CASES, ids=lambda c: "x".join(map(str, c)))
-def test_conv_mfma_parity(torch, case):
+@pytest.mark.parametrize("weights", ["narrow", "own"])
+def test_conv_mfma_parity(torch, case, weights):
+    """Launches this small run on the global-fed kernel with weights that it takes, on
+    the handles' tiles with the others."""
     n, h, w, cin, cout, k, s, bi, bw, wenc, bo, sb, up2 = case
+    bw, wenc = weights_of(weights, bi, bw, wenc)
     check_case(torch, seed=hash(case) % 1000, n=n, h=h, w=w, cin=cin, cout=cout, k=k, stride=s,
                bits_in=bi, bits_w=bw, wenc=wenc, bits_out=bo, skip_bits=sb, skip_up2=up2)
 
@@ -81,15 +85,18 @@ SPLIT_CASES = [
 
 
 @pytest.mark.parametrize("case", SPLIT_CASES, ids=lambda c: "x".join(map(str, c)))
-def test_conv_split_k_parity(torch, case):
+@pytest.mark.parametrize("weights", ["narrow", "own"])
+def test_conv_split_k_parity(torch, case, weights):
     """qconv_run_group_ws with a workspace: the split reduction and the
-    combining epilogue give the oracle's outputs bit for bit, and the same
-    bytes as the unsplit launch."""
+    combining epilogue (8-bit weights; 4-bit ones on 2-bit codes), or the global-fed
+    kernel, which leaves the workspace alone, give the oracle's outputs bit for bit,
+    and the same bytes as the launch without a workspace."""
     n, h, w, cin, cout, k, s, bi, bw, wenc, bo, sb, up2 = case
+    bw, wenc = weights_of(weights, bi, bw, wenc)
     c = workloads.random_conv_case(seed=hash(case) % 1000 + 3, n=n, h=h, w=w, cin=cin, cout=cout,
                                    k=k, stride=s, bits_in=bi, bits_w=bw, wenc=wenc, bits_out=bo,
                                    skip_bits=sb, skip_up2=up2)
-    got = gpu_conv(c, torch, split=True)
+    got = gpu_conv(c, torch, split="parts" if weights == "own" else "whole")
     plain = gpu_conv(c, torch)
     for level, g in enumerate(got):
         assert_same(g, oracle_conv(c, level), f"split {case} level {level}")
@@ -167,7 +174,8 @@ def test_conv_stream_parity(torch, case, variant):
         assert_same(got, oracle_conv(c, level), f"stream {variant} {case} level {level}")
 
 
-# cin a multiple of 256, code outputs and at least 200 tiles of 256 x 128:
+# cin a multiple of 256, code outputs and at least 200 tiles of 256 x 128, with weights
+# that the block-float kernels do not take (those take most of these shapes else):
 # the register-fed kernel (weights read into registers, codes staged in LDS
 # four K steps at a time), on 256 x 64 tiles for K ranges of at most 8
 # steps, on 256 x 144 tiles (one round, one workgroup per CU) where 256 x 128
@@ -213,11 +221,13 @@ def _wv_tiles(case):
 
 @pytest.mark.parametrize("case", WV_CASES, ids=lambda c: "x".join(map(str, c)))
 @pytest.mark.parametrize("variant", ["random_sides", "side0", "small_shifts"])
-def test_conv_register_fed_parity(torch, case, variant):
+@pytest.mark.parametrize("weights", ["narrow", "own"])
+def test_conv_register_fed_parity(torch, case, variant, weights):
     """Per-channel skip sides, all sides 0 (the skip table), and shifts < 2
     (64-bit requantisation)."""
     assert _wv_tiles(case) >= 64 and case[3] % 256 == 0
     n, h, w, cin, cout, k, s, bi, bw, wenc, bo, sb, up2 = case
+    bw, wenc = weights_of(weights, bi, bw, wenc)
     c = workloads.random_conv_case(seed=hash(case) % 1000 + 81, n=n, h=h, w=w, cin=cin, cout=cout,
                                    k=k, stride=s, bits_in=bi, bits_w=bw, wenc=wenc, bits_out=bo,
                                    skip_bits=sb, skip_up2=up2)
@@ -241,9 +251,11 @@ WV_INT32_CASES = [
 
 
 @pytest.mark.parametrize("case", WV_INT32_CASES, ids=lambda c: "x".join(map(str, c)))
-def test_conv_register_fed_int32_parity(torch, case):
+@pytest.mark.parametrize("weights", ["narrow", "own"])
+def test_conv_register_fed_int32_parity(torch, case, weights):
     assert _wv_tiles(case) >= 200 and case[3] % 256 == 0
     n, h, w, cin, cout, k, s, bi, bw, wenc, bo, sb, up2 = case
+    bw, wenc = weights_of(weights, bi, bw, wenc)
     c = workloads.random_conv_case(seed=hash(case) % 1000 + 85, n=n, h=h, w=w, cin=cin, cout=cout,
                                    k=k, stride=s, bits_in=bi, bits_w=bw, wenc=wenc, bits_out=bo)
     for level, got in enumerate(gpu_conv(c, torch)):
@@ -307,11 +319,13 @@ OCC3_CASES = [
 
 @pytest.mark.parametrize("case", OCC3_CASES, ids=lambda c: "x".join(map(str, c)))
 @pytest.mark.parametrize("variant", ["plain", "small_shifts"])
-def test_conv_three_per_cu_parity(torch, case, variant):
+@pytest.mark.parametrize("weights", ["narrow", "own"])
+def test_conv_three_per_cu_parity(torch, case, variant, weights):
     """Shifts < 2 take the 64-bit requantisation."""
     n, h, w, cin, cout, k, s, bo = case
+    bw, wenc = weights_of(weights, 4, 4, 1)
     c = workloads.random_conv_case(seed=hash(case) % 1000 + 41, n=n, h=h, w=w, cin=cin, cout=cout,
-                                   k=k, stride=s, bits_in=4, bits_w=4, wenc=1, bits_out=bo)
+                                   k=k, stride=s, bits_in=4, bits_w=bw, wenc=wenc, bits_out=bo)
     if variant == "small_shifts" and bo != 32:
         rng = np.random.Generator(np.random.PCG64(23))
         for lv in c.levels:
@@ -344,8 +358,10 @@ THREE_BIT_CASES = [
 
 @pytest.mark.parametrize("case", THREE_BIT_CASES, ids=lambda c: "x".join(map(str, c)))
 @pytest.mark.parametrize("variant", ["random_sides", "side0", "small_shifts"])
-def test_three_bit_parity(torch, case, variant):
+@pytest.mark.parametrize("weights", ["narrow", "own"])
+def test_three_bit_parity(torch, case, variant, weights):
     n, h, w, cin, cout, k, s, bi, bw, wenc, bo, sb, up2 = case
+    bw, wenc = weights_of(weights, bi, bw, wenc)
     c = workloads.random_conv_case(seed=hash(case) % 1000 + 61, n=n, h=h, w=w, cin=cin, cout=cout,
                                    k=k, stride=s, bits_in=bi, bits_w=bw, wenc=wenc, bits_out=bo,
                                    skip_bits=sb, skip_up2=up2)
@@ -364,11 +380,13 @@ def test_three_bit_parity(torch, case, variant):
             assert codes.max() == 7
 
 
-def test_three_bit_split_k(torch):
+@pytest.mark.parametrize("weights", ["narrow", "own"])
+def test_three_bit_split_k(torch, weights):
     """Split K with 3-bit codes: the combining epilogue clamps at 7."""
+    bw, wenc = weights_of(weights, 3, 3, 1)
     c = workloads.random_conv_case(seed=71, n=1, h=6, w=7, cin=448, cout=64, k=3, bits_in=3,
-                                   bits_w=3, wenc=1, bits_out=3, skip_bits=3)
-    got = gpu_conv(c, torch, split=True)
+                                   bits_w=bw, wenc=wenc, bits_out=3, skip_bits=3)
+    got = gpu_conv(c, torch, split="parts" if weights == "own" else "whole")
     assert_same(got[0], oracle_conv(c, 0), "3-bit split K")
 
 

@@ -9,7 +9,7 @@ aligned sum u stays inside int32 (the ABI's contract), whatever the inputs.
 import numpy as np
 import pytest
 
-from gpu_helpers import assert_same, gpu_conv, oracle_conv
+from gpu_helpers import assert_same, gpu_conv, oracle_conv, weights_of
 from oracle import ref
 from paper_2007_06919_amd import aqd, workloads
 
@@ -110,8 +110,11 @@ EDGE_CASES = [
 
 
 @pytest.mark.parametrize("case", EDGE_CASES, ids=lambda c: "x".join(map(str, c)))
-def test_edge_ranges_parity(torch, case):
-    c = edge_case(hash(case) % 1000 + 31, *case)
+@pytest.mark.parametrize("weights", ["narrow", "own"])
+def test_edge_ranges_parity(torch, case, weights):
+    """On the global-fed kernel, and on the handles' own tiles."""
+    bw, wenc = weights_of(weights, *case[7:10])
+    c = edge_case(hash(case) % 1000 + 31, *case[:8], bw, wenc, *case[10:])
     for level, got in enumerate(gpu_conv(c, torch)):
         assert_same(got, oracle_conv(c, level), f"edge ranges {case} level {level}")
 
@@ -124,9 +127,11 @@ SPLIT_EDGE_CASES = [
 
 
 @pytest.mark.parametrize("case", SPLIT_EDGE_CASES, ids=lambda c: "x".join(map(str, c)))
-def test_edge_ranges_split_k(torch, case):
-    c = edge_case(hash(case) % 1000 + 37, *case)
-    for level, got in enumerate(gpu_conv(c, torch, split=True)):
+@pytest.mark.parametrize("weights", ["narrow", "own"])
+def test_edge_ranges_split_k(torch, case, weights):
+    bw, wenc = weights_of(weights, *case[7:10])
+    c = edge_case(hash(case) % 1000 + 37, *case[:8], bw, wenc, *case[10:])
+    for level, got in enumerate(gpu_conv(c, torch, split="parts" if weights == "own" else "whole")):
         assert_same(got, oracle_conv(c, level), f"split edge ranges {case} level {level}")
 
 

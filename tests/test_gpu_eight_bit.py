@@ -46,6 +46,10 @@ B8_CASES = [
     (2, 20, 33, 128, 36, 3, 1),      # box predictor shape, 128 input channels
     (1, 25, 40, 384, 256, 1, 1),     # 1x1, three stages per tap
     (3, 17, 13, 256, 512, 3, 2),     # stride 2, ragged pixel tail
+    # (those run on the global-fed kernel; more than 512 tiles of 64 x 64 on 256 x 128 tiles)
+    (1, 60, 75, 128, 720, 3, 1),     # a partial channel tile
+    (1, 90, 95, 256, 256, 1, 1),     # two stages
+    (3, 111, 113, 128, 516, 1, 2),   # stride 2, ragged pixel tail
 ]
 
 
@@ -57,9 +61,12 @@ def test_eight_bit_codes_on_mfma(torch, case):
     assert_same(gpu_conv(c, torch)[0], oracle_conv(c), f"8-bit {case}")
 
 
-def test_eight_bit_split_k(torch):
-    c = _case(5, 1, 9, 13, 1024, 256, 3, 1, 8, 8, TWOS, 32)
-    assert_same(gpu_conv(c, torch, split=True)[0], oracle_conv(c), "8-bit split K")
+@pytest.mark.parametrize("shape, split", [((1, 9, 13, 1024, 256, 3), "whole"), ((1, 84, 100, 512, 256, 3), "parts")])
+def test_eight_bit_split_k(torch, shape, split):
+    """A long K range: on the global-fed kernel while the tiles are few, in parts above."""
+    n, h, w, cin, cout, k = shape
+    c = _case(5, n, h, w, cin, cout, k, 1, 8, 8, TWOS, 32)
+    assert_same(gpu_conv(c, torch, split=split)[0], oracle_conv(c), "8-bit split K")
 
 
 def test_eight_bit_extremes(torch):

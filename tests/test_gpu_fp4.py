@@ -1,8 +1,9 @@
-"""GPU parity of the 2-bit path on the scaled FP4 MFMA (e2m1 operands, fp32
-sums of integers): code outputs with and without 2-bit skips (per-channel
-sides, the side-0 table, upsampled), shifts < 2 (64-bit requantisation),
-int32 outputs, split K ranges, grouped multi-level launches, and the largest
-sums the path admits, all bit-exact against the oracle."""
+"""GPU parity of the 2-bit layers of handles on the FP4 path (2-bit codes and weights,
+channels in multiples of 256), which run on the block-float kernels with e2m1
+operands and fp32 sums of integers: code outputs with and without 2-bit skips
+(per-channel sides, the side-0 table, upsampled), shifts < 2 (64-bit
+requantisation), int32 outputs, long K ranges on few tiles, grouped multi-level
+launches, and the largest sums the path admits, all bit-exact against the oracle."""
 import numpy as np
 import pytest
 
@@ -79,7 +80,8 @@ def test_fp4_int32_parity(torch, case):
 
 
 FP4_SPLIT_CASES = [
-    # few tiles, long K: the split-K parts run on the FP4 kernel
+    # few tiles, long K: the handle asks for a workspace; the global-fed kernel splits K
+    # between the waves of a tile and leaves it alone
     (1, 13, 21, 1024, 256, 3, 1, 2, 2, 1, 2, 2, False),
     (1, 7, 11, 2048, 512, 3, 2, 2, 2, 0, 2, 0, False),
     (2, 9, 10, 2048, 256, 1, 1, 2, 2, 1, 2, 2, True),
@@ -93,7 +95,7 @@ def test_fp4_split_k_parity(torch, case):
                                    stride=s, bits_in=bi, bits_w=bw, wenc=wenc, bits_out=bo,
                                    skip_bits=sb, skip_up2=up2)
     assert _path(c) == "fp4-mfma"
-    for level, got in enumerate(gpu_conv(c, torch, split=True)):
+    for level, got in enumerate(gpu_conv(c, torch, split="whole")):
         assert_same(got, oracle_conv(c, level), f"fp4 split {case} level {level}")
 
 
@@ -158,11 +160,38 @@ def test_fp4_grouped_levels_and_guard_bytes(torch):
 
 
 def test_two_bit_layers_off_the_fp4_path(torch):
-    """2-bit layers the FP4 kernel does not take (cout not a multiple of 256,
-    4-bit weights, an int32 skip) report the int8 path and stay exact."""
+    """2-bit layers off the FP4 path (cout not a multiple of 256, 4-bit weights, an
+    int32 skip) report the int8 path and stay exact."""
     for kw in (dict(cin=256, cout=128, bits_w=2, skip_bits=0),
                dict(cin=256, cout=256, bits_w=4, skip_bits=0),
                dict(cin=256, cout=256, bits_w=2, skip_bits=32)):
         c = workloads.random_conv_case(seed=3, n=1, h=17, w=19, k=3, bits_in=2, wenc=1, bits_out=2, **kw)
         assert _path(c) == "i8-mfma", kw
         assert_same(gpu_conv(c, torch)[0], oracle_conv(c), f"int8 path {kw}")
+
+
+def test_handles_of_different_layouts_are_refused_in_one_group(torch, monkeypatch):
+    """AQD_NO_FP4=1 at create lays a 2-bit handle's weights out for the int8 tiles."""
+    c = workloads.random_conv_case(seed=4, n=1, h=5, w=6, cin=256, cout=256, k=1, bits_in=2, bits_w=2, wenc=1, bits_out=2)
+
+    def create():
+        return aqd.qconv_create(256, 256, 1, 1, 0, 2, 2, aqd.pack_codes(c.w_fields, 2), c.levels, wenc=1, bits_out=2)
+
+    handles = [create()]
+    monkeypatch.setenv("AQD_NO_FP4", "1")
+    handles.append(create())
+    try:
+        x = torch.from_numpy(aqd.pack_codes(c.x, 2)).to("cuda:0")
+        ys = [torch.zeros((1, 5, 6, 64), dtype=torch.uint8, device="cuda:0") for _ in range(2)]
+        segs = [(h, 0, 1, 5, 6, x, None, 0, 0, y) for h, y in zip(handles, ys)]
+        with pytest.raises(aqd.AqdError) as e:
+            aqd.qconv_run_group(segs)
+        assert e.value.status == aqd.AQD_ERR_INVALID
+        for s in segs:
+            aqd.qconv_run_group([s])
+        torch.cuda.synchronize()
+        for y in ys:
+            assert_same(y.cpu().numpy(), oracle_conv(c), "each alone")
+    finally:
+        for h in handles:
+            aqd.qconv_destroy(h)

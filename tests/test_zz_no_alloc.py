@@ -6,7 +6,7 @@ both against the oracle."""
 import numpy as np
 import pytest
 
-from gpu_helpers import assert_same, oracle_conv
+from gpu_helpers import assert_same, oracle_conv, weights_of
 from paper_2007_06919_amd import aqd, workloads
 
 pytestmark = pytest.mark.gpu
@@ -47,13 +47,17 @@ CASES = [
 
 
 @pytest.mark.parametrize("pair", CASES, ids=["p6_code_skip", "int32_out", "int32_skip"])
-def test_static_scratch_matches_workspace(torch, pair):
+@pytest.mark.parametrize("weights", ["narrow", "own"])
+def test_static_scratch_matches_workspace(torch, pair, weights):
+    """With 8-bit weights the launches split; with 4-bit ones the global-fed kernel takes
+    them and leaves scratch and workspace alone."""
     for call, (n, h, w, cin, cout, k, s, wenc, bo, sb, up2) in enumerate(pair):
+        bw, wenc = weights_of(weights, 4, 4, wenc)
         case = workloads.random_conv_case(seed=900 + 10 * call + cin % 7, n=n, h=h, w=w, cin=cin,
-                                          cout=cout, k=k, stride=s, bits_in=4, bits_w=4, wenc=wenc,
+                                          cout=cout, k=k, stride=s, bits_in=4, bits_w=bw, wenc=wenc,
                                           bits_out=bo, skip_bits=sb, skip_up2=up2)
         out_mode = aqd.OUT_INT32 if bo == 32 else aqd.OUT_CODES
-        hd = aqd.qconv_create(cin, cout, k, s, k // 2, 4, 4, aqd.pack_codes(case.w_fields, 4),
+        hd = aqd.qconv_create(cin, cout, k, s, k // 2, 4, bw, aqd.pack_codes(case.w_fields, bw),
                               case.levels, wenc=wenc, out_mode=out_mode,
                               bits_out=0 if bo == 32 else bo, skip_bits=sb, skip_up2=up2)
         try:
@@ -65,6 +69,7 @@ def test_static_scratch_matches_workspace(torch, pair):
             aqd.qconv_run_group_static(segs)
             aqd.qconv_run_group_ws([(hd, 0, n, h, w, x, skip, hs, ws, y_ws)], wsbuf, nbytes)
             torch.cuda.synchronize()
+            assert bool((wsbuf != 0x77).any()) == (weights == "own")
             got, ref_ws = y_static.cpu().numpy(), y_ws.cpu().numpy()
             assert_same(got, ref_ws, f"static vs workspace, call {call}")
             assert_same(got, oracle_conv(case), f"static vs oracle, call {call}")
