@@ -200,16 +200,19 @@ aqd_status_t qconv_run_group(int count, const qconv_seg_t *segs, aqd_stream_t st
  * qconv_group_workspace: *bytes receives the device workspace size with
  * which qconv_run_group_ws may split this group's reduction over several
  * workgroups; 0 when the group is not worth splitting (its launch already
- * fills the GPU). The size depends on the handles' shapes and on n, h, w of
- * every segment, not on the tensor pointers. Errors as qconv_run_group.
+ * fills the GPU). The size is that of the handles' own kernel (qconv_path): it
+ * depends on the handles' shapes and on n, h, w of every segment, not on the
+ * tensor pointers, and is an upper bound of what the launch uses. Errors as
+ * qconv_run_group.
  *
  * qconv_run_group_ws: as qconv_run_group. With workspace non-NULL and
- * ws_bytes at least the queried size (and the size non-zero), the K range of
- * every output tile is cut into parts whose int32 partial sums go to the
- * workspace, and a second kernel adds the parts and applies the epilogue;
- * the outputs are identical to qconv_run_group's. Otherwise the call is
- * exactly qconv_run_group. The workspace is scratch (device memory owned by
- * the caller, 256-byte aligned, contents irrelevant on entry and undefined
+ * ws_bytes at least the queried size (and the size non-zero), a launch on the
+ * handles' own kernel cuts the K range of every output tile into parts whose
+ * int32 partial sums go to the workspace, and a second kernel adds the parts
+ * and applies the epilogue; a launch on the block-float kernels leaves the
+ * workspace alone. The outputs are identical to qconv_run_group's. Otherwise the
+ * call is exactly qconv_run_group. The workspace is scratch (device memory owned
+ * by the caller, 256-byte aligned, contents irrelevant on entry and undefined
  * on return); calls that share a workspace must not overlap in time (use one
  * stream, or one workspace per stream). */
 aqd_status_t qconv_group_workspace(int count, const qconv_seg_t *segs, size_t *bytes);
@@ -222,9 +225,10 @@ aqd_status_t qconv_run_group_ws(int count, const qconv_seg_t *segs, void *worksp
  * uses a scratch array of AQD_STATIC_SCRATCH_BYTES (64 MiB) that the library
  * holds on each GPU it runs on, until the process ends; the call allocates
  * nothing. Outputs are identical to qconv_run_group_ws's with a workspace of
- * the queried size. A group whose split would need more scratch than that
- * returns AQD_ERR_UNSUPPORTED (the message names the size) with no launch;
- * run it with qconv_run_group_ws instead. Every call on one GPU shares that
+ * the queried size. A group whose handles' own kernel would need more scratch
+ * than that to split (the size of qconv_group_workspace) returns
+ * AQD_ERR_UNSUPPORTED (the message names the size) with no launch, whichever
+ * kernel the launch would run on; run it with qconv_run_group_ws instead. Every call on one GPU shares that
  * GPU's scratch and leaves its contents behind: calls that overlap in time on
  * one GPU (on two streams, or from two threads) race; serialise them on one
  * stream. Other errors as qconv_run_group. */
@@ -255,16 +259,18 @@ void qconv_destroy(qconv_t conv);
 
 /* The arithmetic of a handle's own kernel, fixed at create: "fp4-mfma"
  * (2-bit codes and 2-bit weights with cin and cout multiples of 256, exact
- * while K * 3 * max|w| < 2^24: the FP4 MFMA with e2m1 operands and fp32 sums
- * of integers), "i8-mfma" (codes widened to int8 on the int8 MFMA), "direct"
- * (every other shape: one thread per output). Small launches, and launches
- * that would run on the direct kernel, take a kernel that reads its operands
- * straight from global memory where the shape allows (cin a multiple of 32,
- * or of 16 for 8-bit codes): e2m3 or e2m1 operands with fp32 sums of integers
- * below 2^24, int8 ones for 8-bit codes; the same results bit for bit. A static
+ * while K * 3 * max|w| < 2^24: the block-float MFMA with e2m1 operands and fp32
+ * sums of integers), "i8-mfma" (codes widened to int8 on the int8 MFMA), "direct"
+ * (every other shape: one thread per output). It is not what every launch runs on:
+ * launches of 2- to 4-bit codes with weights of at most 4 bits, cin a multiple of 32
+ * and sums below 2^24 run on the block-float MFMA (e2m3 or e2m1 operands, fp32 sums
+ * of integers) wherever that measured faster, which takes in most 3x3 layers and all
+ * of the "fp4-mfma" handles'; 8-bit codes with cin a multiple of 16 take an int8
+ * kernel that reads its operands straight from global memory when the launch is small
+ * or the handle is "direct". Every route gives the same results bit for bit. A static
  * string; "invalid" for a null handle. With the environment variable
- * AQD_NO_FP4=1 at create, 2-bit layers' own kernel is the int8 MFMA's (the same
- * results; for comparing the two). */
+ * AQD_NO_FP4=1 at create, 2-bit layers stay on the int8 MFMA (the same results; for
+ * comparing the two); a group takes handles created with or without it, not both. */
 const char *qconv_path(qconv_t conv);
 
 /* Standalone integer skip connection (Sec. 3.2.3, Eq. 7) with

@@ -207,8 +207,8 @@ def qconv_run_group(segs, stream=None):
 
 
 def qconv_group_workspace(segs) -> int:
-    """Workspace bytes with which qconv_run_group_ws splits the K reduction
-    of this group (0: never split)."""
+    """Workspace bytes with which qconv_run_group_ws may split the K reduction
+    of this group (0: never split; see aqd.h)."""
     b = ctypes.c_size_t(0)
     _check(lib().qconv_group_workspace(len(segs), _seg_array(segs), ctypes.byref(b)))
     return b.value
