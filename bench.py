@@ -40,8 +40,8 @@ B2B_REPS = 10               # back-to-back repeats of each dominant launch (sust
 # COPY_PROBE_BYTES; valid only for the kernel source it was measured on.
 HEAD_KERNEL = "qconv_fx3_kernel<1, 4, 8, 0, 0, 2, 8, 0>"
 HEAD_KERNEL_SOURCES = ("qconv_fx.hip", "mfma_common.h")
-HEAD_TRAFFIC = {"kernel_sha256": "23c7ab5bcd093f7e56441d5adc575604bff49791611d4929f4f4c87e5d82f536",
-                "fetch_bytes": 49784944, "write_bytes": 45670400}
+HEAD_TRAFFIC = {"kernel_sha256": "8445b99b262899de2a66877d9b6959d1253997ea5b53498a1cdc070f3023caa7",
+                "fetch_bytes": 49780848, "write_bytes": 45670400}
 
 
 def kernel_sha256():
@@ -176,8 +176,8 @@ def pct(v, q):
 def fp4_layer(args):
     """The 2-bit head-tower launch (class and box towers' 3x3 256 -> 256 layer
     over P3-P7 of a batch of eight 800x1333 images: 10 segments, one grouped
-    launch) on the FP4 MFMA path and on the int8 MFMA path (handles created
-    with AQD_NO_FP4=1); both outputs must agree byte for byte."""
+    launch) on the block-float MFMA with e2m1 operands and on the int8 MFMA (handles
+    created with AQD_NO_FP4=1); both outputs must agree byte for byte."""
     import numpy as np
     import torch
     from paper_2007_06919_amd import aqd, workloads
@@ -313,7 +313,10 @@ def main():
     from paper_2007_06919_amd import aqd
     path = {gi: aqd.qconv_path(gpu.handles[gpu.schedule[gi][0][0].name])
             if gpu.schedule[gi][0][0].op == "conv" else gpu.schedule[gi][0][0].op for gi in live}
-    peak = {gi: MFMA_FP4_PEAK_TOPS if path[gi] == "fp4-mfma" else MFMA_I8_PEAK_TOPS for gi in live}
+    # the rate of the fastest matrix instructions that hold a launch's operands exactly,
+    # whichever kernel it runs on: e2m3 or e2m1 up to 4 bits, int8 above
+    peak = {gi: MFMA_I8_PEAK_TOPS if net.tensors[gpu.schedule[gi][0][0].segs[0][0]].bits == 8 else MFMA_FP4_PEAK_TOPS
+            for gi in live}
     events = {}
 
     def hook(gi, when, s):
@@ -383,7 +386,7 @@ def main():
         per_launch.append({
             "launch": "+".join(sorted({c.name for c, _ in gpu.schedule[gi]})),
             "segments": len(gpu.schedule[gi]), "shape": f"{conv0.k}x{conv0.k} {conv0.cin}->{conv0.cout}",
-            "path": path[gi],
+            "handle_path": path[gi], "peak_tops": peak[gi],
             "us": round(us, 2), "int_tops": round(ops / us / 1e6, 1),
             "gbs": round(nbytes / us / 1e3, 1), "bound": bound,
             "frac": round(max(t_mfma, t_hbm) / us, 4),
@@ -394,7 +397,7 @@ def main():
     avg_us = float(np.mean(durs))
     b2b_us = 1e3 * b0.elapsed_time(b1) / (B2B_REPS * len(dominant))
     achieved = avg_ops / (avg_us / 1e6) / 1e12
-    dom_peak = MFMA_FP4_PEAK_TOPS   # the head towers run on e2m3 operands
+    dom_peak = peak[dominant[0]]
     log(f"[bench] {ms_step:.3f} ms/step as a graph replay (median {np.median(step_ms):.3f}, "
         f"p10 {pct(step_ms, 10):.3f}, p90 {pct(step_ms, 90):.3f}; wall "
         f"{wall / args.steps * 1e3:.3f} ms; {serial_ms_step:.3f} ms launch by launch on one "
@@ -404,7 +407,8 @@ def main():
         "metric": METRIC, "value": round(value, 3), "unit": "int TOPS", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_step, 4),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "i8", "data": "synthetic",
+        "dtype": f"int{args.bits} codes, exact on {'e2m1' if args.bits == 2 else 'e2m3'} and int8 MFMA",
+        "data": "synthetic",
         "config": {"workload": workload, "batch": n_img, "image": [800, 1333],
                    "bits": args.bits, "conv_segments": sum(len(c.segs) for c in net.convs),
                    "launches_per_step": gpu.launches_per_forward(), "int_ops_per_step": total_ops,
@@ -432,7 +436,9 @@ def main():
     out["roofline"]["traffic"] = traffic
     gpu.close()
     out["measured_peaks"] = measured_peaks(torch, dev)
-    # (e2m3 operands: twice the measured int8 rate)
+    # no probe of its own for e2m3 operands: their instruction does twice the int8 one's work
+    # in the same time
+    out["roofline"]["measured_mfma"] = "twice measured_peaks.mfma_i8_tops"
     out["roofline"]["frac_of_measured_mfma"] = round(achieved / (2 * out["measured_peaks"]["mfma_i8_tops"]), 4)
     if args.copy_probe:
         src = torch.ones(COPY_PROBE_BYTES, dtype=torch.uint8, device=dev)
